@@ -67,7 +67,7 @@ typedef int32_t dg_status;
 
 /* Kernel bodies of the forward product (same results, different data movement). */
 #define DG_BODY_STAGED 0      /* D in LDS, u and out staged through LDS per wave (memory-bound orders) */
-#define DG_BODY_CHUNKREG 1    /* D held in registers, one output chunk per wave (matrix-core-bound orders) */
+#define DG_BODY_CHUNKREG 1    /* D held in registers, the workgroup shares its tiles (matrix-core-bound orders) */
 #define DG_BODY_STAGED_LEAN 2 /* as STAGED with at most 128 registers a lane (two 8-wave workgroups per CU) */
 
 /* Variant (launch shape) selection: DG_VARIANT_AUTO is the library's default. */
@@ -249,8 +249,11 @@ dg_status dg_volume_batched(const dg_group *groups, int32_t ngroups, int32_t F, 
  * the workgroup shares its tiles), the waves per workgroup, and the 16-column
  * tiles one loop iteration takes (per wave for the staged body, per workgroup
  * for the chunk-register body).  Variant 0 is the default that dg_volume and
- * dg_volume_f32s use; the others are the autotuner's search space (the paper's
+ * dg_volume_f32s use, except in FP64 at Np = 56, where it is variant 1 up to
+ * 2^18 columns (K F); the others are the autotuner's search space (the paper's
  * autotuning use case, Introduction and Section 3, applied to tile shapes).
+ * A single-group launch may run a variant's wave groups as workgroups of their
+ * own; the description below is that of a batched launch.
  */
 typedef struct dg_variant_info {
   int32_t body;          /* DG_BODY_STAGED, DG_BODY_CHUNKREG or DG_BODY_STAGED_LEAN */

@@ -14,6 +14,7 @@
 #include "dgvol.h"
 #include "dgvol_device.hpp"
 #include "dgvol_forward.hpp"
+#include "dgvol_forward_direct.hpp"
 #include "dgvol_forward_f32s.hpp"
 #include "dgvol_layout.hpp"
 #include "dgvol_variants.hpp"
@@ -28,10 +29,17 @@ constexpr int BODY_CHUNKREG = DG_BODY_CHUNKREG;
 constexpr int BODY_LEAN = DG_BODY_STAGED_LEAN;
 static_assert(BODY_STAGED == VB_S && BODY_CHUNKREG == VB_C && BODY_LEAN == VB_L, "body ids of the variant tables");
 
+// Whether a variant runs the body that stores from its accumulators (dgvol_forward_direct.hpp).
+template <int NP, int BODY, int TILES>
+constexpr bool f64_direct() { return BODY == BODY_CHUNKREG && (NP == 120 || (NP >= 56 && TILES == 2)); }
+
 // Dynamic LDS of one workgroup of a variant.
 template <int NP, int BODY, int WPB, int TILES>
 constexpr int f64_lds() {
-  return BODY != BODY_CHUNKREG ? fwd_f64_staged_lds<NP, WPB, TILES>() : fwd_f64_chunkreg_lds<NP, WPB, TILES>();
+  if constexpr (f64_direct<NP, BODY, TILES>())
+    return fwd_f64_direct_lds<NP, WPB, TILES>();
+  else
+    return BODY != BODY_CHUNKREG ? fwd_f64_staged_lds<NP, WPB, TILES>() : fwd_f64_chunkreg_lds<NP, WPB, TILES>();
 }
 template <int NP, int BODY, int WPB, int TILES>
 constexpr int f32s_lds() {
@@ -54,6 +62,8 @@ __device__ __forceinline__ void fwd_f64_body(const FwdArgs<double>& p, uint32_t 
     fwd_f64_staged_body<NP, WPB, TILES, true>(p, bid, nblk, lds);
   else if constexpr (BODY == BODY_STAGED)
     fwd_f64_staged_body<NP, WPB, TILES>(p, bid, nblk, lds);
+  else if constexpr (f64_direct<NP, BODY, TILES>())
+    fwd_f64_direct_body<NP, WPB, TILES>(p, bid, nblk, lds);
   else
     fwd_f64_chunkreg_body<NP, WPB, TILES>(p, bid, nblk, lds);
 }
@@ -71,6 +81,17 @@ __device__ __forceinline__ void fwd_f32s_body(const FwdArgs<float>& p, uint32_t 
 // CU); without the bound the compiler takes registers up to one wave per SIMD.
 // The lean staged body is held to 128 (two 8-wave workgroups per CU).
 constexpr int min_waves_per_eu(int wpb, int body = VB_S) { return body == VB_L ? 4 : wpb == 4 ? 3 : 1; }
+
+// A single-group launch of a direct body whose waves form two halves (one
+// column tile each per iteration) runs every half as a workgroup of its own,
+// with its own barriers: order 6 at 3e6 nodal values 40.2 -> 35.6 us, order 5
+// 28.9 -> 27.1 us.  In the batched kernel the halves share a workgroup.
+template <int NP, int WPB, int TILES>
+__global__ __launch_bounds__(WAVE* WPB) __attribute__((amdgpu_waves_per_eu(2, 8))) void fwd_f64_direct_kernel(
+    FwdArgs<double> p) {
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  fwd_f64_direct_body<NP, WPB, TILES>(p, blockIdx.x, gridDim.x, lds);
+}
 
 template <int NP, int BODY, int WPB, int TILES>
 __global__ __launch_bounds__(WAVE* WPB)

@@ -120,22 +120,38 @@ static inline uint32_t ceil_div(uint64_t a, uint64_t b) { return (uint32_t)((a +
 struct VariantDesc {
   const void* fn;  // its single-group kernel
   int body;
-  int wpb;
+  int wpb;         // waves, tiles per iteration and LDS of its workgroups in a batched launch
   int tiles;
   int cls;
   int lds;
+  int wpb1;        // the same in a single-group launch
+  int tiles1;
+  int lds1;
 };
+
+template <int NP, int BODY, int WPB, int TILES, int CLS>
+static VariantDesc f64_desc() {
+  if constexpr (f64_direct<NP, BODY, TILES>()) {
+    using S = DirectShape<NP, WPB>;
+    constexpr int W1 = S::UNITS, T1 = TILES / S::HALVES;
+    return VariantDesc{reinterpret_cast<const void*>(fwd_f64_direct_kernel<NP, W1, T1>), BODY, WPB, TILES, CLS,
+                       f64_lds<NP, BODY, WPB, TILES>(), W1, T1, fwd_f64_direct_lds<NP, W1, T1>()};
+  } else {
+    constexpr int lds = f64_lds<NP, BODY, WPB, TILES>();
+    return VariantDesc{reinterpret_cast<const void*>(fwd_f64_kernel<NP, BODY, WPB, TILES>), BODY, WPB, TILES, CLS,
+                       lds, WPB, TILES, lds};
+  }
+}
 
 static bool variant_desc(int form, int Np, int v, VariantDesc* d) {
 #define DGVOL_VDESC64(NP, IDX, BODY, WPB, TILES, CLS)                                                   \
   case vkey(NP, IDX):                                                                                   \
-    *d = VariantDesc{reinterpret_cast<const void*>(fwd_f64_kernel<NP, BODY, WPB, TILES>), BODY, WPB, TILES, \
-                     CLS, f64_lds<NP, BODY, WPB, TILES>()};                                             \
+    *d = f64_desc<NP, BODY, WPB, TILES, CLS>();                                                         \
     return true;
 #define DGVOL_VDESC32(NP, IDX, BODY, WPB, TILES, CLS)                                                    \
   case vkey(NP, IDX):                                                                                    \
     *d = VariantDesc{reinterpret_cast<const void*>(fwd_f32s_kernel<NP, BODY, WPB, TILES>), BODY, WPB, TILES, \
-                     CLS, f32s_lds<NP, BODY, WPB, TILES>()};                                             \
+                     CLS, f32s_lds<NP, BODY, WPB, TILES>(), WPB, TILES, f32s_lds<NP, BODY, WPB, TILES>()};  \
     return true;
   if (v < 0 || v >= 16) return false;
   if (form == DG_FORM_F64) {
@@ -147,6 +163,19 @@ static bool variant_desc(int form, int Np, int v, VariantDesc* d) {
   return false;
 #undef DGVOL_VDESC64
 #undef DGVOL_VDESC32
+}
+
+// The variant DG_VARIANT_AUTO selects, for a group on its own and in a batch: the first of
+// its list, except for FP64 at order 5 up to 2^18 columns, where the direct
+// body (variant 1) takes over.  Its stores are 128-byte runs that straddle
+// cache lines: while the three planes stay in the 256 MB memory-side cache
+// they cost nothing and its short start (D straight into registers) wins:
+// 20.0 -> 10.5 us at 150 thousand nodal values, 34.9 -> 27.5 us at 3e6, 83.8
+// -> 78.7 us at 1e7.  Past it the staged body's full-line streaming stores
+// win (2.2e7: 165.7 against 171.3 us; 9e7: 631 against 678 us).
+constexpr uint64_t DIRECT56_MAX_COLS = 1u << 18;
+static int auto_variant(int form, int Np, uint64_t ncols) {
+  return form == DG_FORM_F64 && Np == 56 && ncols <= DIRECT56_MAX_COLS ? 1 : 0;
 }
 
 static int variant_count(int form, int Np) {
@@ -166,6 +195,10 @@ static inline uint32_t units_per_step(const VariantDesc& d) {
 }
 static inline uint32_t workers_per_block(const VariantDesc& d) {
   return d.body != BODY_CHUNKREG ? (uint32_t)d.wpb : 1u;
+}
+// ... in a single-group launch
+static inline uint32_t units_per_step1(const VariantDesc& d) {
+  return d.body != BODY_CHUNKREG ? (uint32_t)(d.wpb1 * d.tiles1) : (uint32_t)d.tiles1;
 }
 
 // The batched kernel of a launch class.
@@ -195,10 +228,10 @@ static inline int launch_class(const VariantDesc& d, bool by_class) {
 
 // Persistent grid of a single-group launch of variant d over `ntiles` tiles.
 static uint32_t single_grid(const VariantDesc& d, uint32_t ntiles, int* err, uint32_t* resident) {
-  const int cap = resident_blocks_fn(d.fn, WAVE * d.wpb, d.lds, err);
+  const int cap = resident_blocks_fn(d.fn, WAVE * d.wpb1, d.lds1, err);
   if (*err != DG_OK) return 0;
   if (resident) *resident = (uint32_t)cap;
-  return std::min<uint32_t>(ceil_div(ntiles, units_per_step(d)), (uint32_t)cap);
+  return std::min<uint32_t>(ceil_div(ntiles, units_per_step1(d)), (uint32_t)cap);
 }
 
 template <typename T>
@@ -208,7 +241,7 @@ static dg_status launch_variant(const VariantDesc& d, const FwdArgs<T>& p, hipSt
   if (err != DG_OK) return err;
   FwdArgs<T> a = p;
   void* args[] = {&a};
-  if (hipLaunchKernel(d.fn, dim3(grid), dim3(WAVE * d.wpb), args, (size_t)d.lds, stream) != hipSuccess)
+  if (hipLaunchKernel(d.fn, dim3(grid), dim3(WAVE * d.wpb1), args, (size_t)d.lds1, stream) != hipSuccess)
     return DG_ELAUNCH;
   return hipGetLastError() == hipSuccess ? DG_OK : DG_ELAUNCH;
 }
@@ -231,9 +264,9 @@ static double tile_cost_estimate(int form, int Np, uint32_t F) {
     case 10: eff = form == DG_FORM_F64 ? 0.65 : 0.65; break;
     case 20: eff = form == DG_FORM_F64 ? 0.67 : 0.60; break;
     case 35: eff = form == DG_FORM_F64 ? 0.60 : 0.55; break;
-    case 56: eff = form == DG_FORM_F64 ? 0.58 : 0.76; break;
-    case 84: eff = form == DG_FORM_F64 ? 0.54 : 0.70; break;
-    default: eff = form == DG_FORM_F64 ? 0.60 : 0.55; break;  // Np = 120
+    case 56: eff = form == DG_FORM_F64 ? 0.60 : 0.76; break;
+    case 84: eff = form == DG_FORM_F64 ? 0.64 : 0.70; break;
+    default: eff = form == DG_FORM_F64 ? 0.68 : 0.55; break;  // Np = 120
   }
   return std::max(bytes / bw, flops / peak) / eff;
 }
@@ -456,7 +489,8 @@ dg_status dg_volume_variant(int32_t form, int32_t variant, const void* D, const 
   if (st != DG_OK) return st;
   if (form != DG_FORM_F64 && form != DG_FORM_F32S) return DG_EUNSUPPORTED;
   VariantDesc d;
-  if (!variant_desc(form, Np, variant == DG_VARIANT_AUTO ? 0 : variant, &d)) return DG_EUNSUPPORTED;
+  const int v = variant == DG_VARIANT_AUTO ? auto_variant(form, Np, (uint64_t)K * (uint64_t)F) : variant;
+  if (!variant_desc(form, Np, v, &d)) return DG_EUNSUPPORTED;
   if (noop) return DG_OK;
   const uintptr_t word = form == DG_FORM_F64 ? 8 : 4;
   if (!D || !G || !u || !out) return DG_EINVAL;
@@ -555,13 +589,14 @@ dg_status dg_volume_batched(const dg_group* groups, int32_t ngroups, int32_t F, 
   // validate everything first (nothing is launched on error), then one launch per class
   VariantDesc desc[DG_MAX_GROUPS];
   bool live[DG_MAX_GROUPS];
+  int32_t variant[DG_MAX_GROUPS];
   for (int i = 0; i < ngroups; ++i) {
     const dg_group& gr = groups[i];
     bool noop = false;
     const dg_status st = check_common(gr.K, gr.Np, F, &noop);
     if (st != DG_OK) return st;
-    if (!variant_desc(form, gr.Np, gr.variant == DG_VARIANT_AUTO ? 0 : gr.variant, &desc[i]))
-      return DG_EUNSUPPORTED;
+    variant[i] = gr.variant == DG_VARIANT_AUTO ? auto_variant(form, gr.Np, (uint64_t)gr.K * (uint64_t)F) : gr.variant;
+    if (!variant_desc(form, gr.Np, variant[i], &desc[i])) return DG_EUNSUPPORTED;
     live[i] = !noop;
     if (noop) continue;
     if (!gr.D || !gr.G || !gr.u || !gr.out) return DG_EINVAL;
@@ -582,7 +617,7 @@ dg_status dg_volume_batched(const dg_group* groups, int32_t ngroups, int32_t F, 
       const uint64_t ncols = (uint64_t)gr.K * (uint64_t)F;
       GroupDev& gd = a.g[ng];
       gd.Np = gr.Np;
-      gd.variant = gr.variant == DG_VARIANT_AUTO ? 0 : gr.variant;
+      gd.variant = variant[i];
       gd.ncols = (uint32_t)ncols;
       gd.ntiles = ceil_div(ncols, 16);
       gd.plane = (int64_t)ncols * gr.Np;
@@ -651,13 +686,17 @@ dg_status dg_launch_shape_query(int32_t op, int32_t form, int32_t Np, int32_t va
   dg_launch_shape sh{};
   if (op == DG_OP_FORWARD || op == DG_OP_BATCHED || op == DG_OP_BATCHED_BY_CLASS) {
     VariantDesc d;
-    if (!variant_desc(form, Np, variant == DG_VARIANT_AUTO ? 0 : variant, &d)) return DG_EUNSUPPORTED;
+    const int v = variant == DG_VARIANT_AUTO ? auto_variant(form, Np, (uint64_t)K * (uint64_t)F) : variant;
+    if (!variant_desc(form, Np, v, &d)) return DG_EUNSUPPORTED;
     const uint32_t ntiles = ceil_div((uint64_t)K * (uint64_t)F, 16);
-    const uint32_t per = units_per_step(d);
+    const bool single = op == DG_OP_FORWARD;
+    const uint32_t per = single ? units_per_step1(d) : units_per_step(d);
+    const uint32_t tiles = (uint32_t)(single ? d.tiles1 : d.tiles);
+    const int lds = single ? d.lds1 : d.lds;
     uint32_t cap = 0;
-    if (op == DG_OP_FORWARD) {
-      cap = (uint32_t)resident_blocks_fn(d.fn, WAVE * d.wpb, d.lds, &err);
-      sh.block = WAVE * d.wpb;
+    if (single) {
+      cap = (uint32_t)resident_blocks_fn(d.fn, WAVE * d.wpb1, lds, &err);
+      sh.block = WAVE * d.wpb1;
     } else {
       const int lc = launch_class(d, op == DG_OP_BATCHED_BY_CLASS);
       sh.block = WAVE * class_waves(lc);
@@ -665,12 +704,12 @@ dg_status dg_launch_shape_query(int32_t op, int32_t form, int32_t Np, int32_t va
     }
     if (err != DG_OK) return err;
     sh.grid = std::min<uint32_t>(ceil_div(ntiles, per), cap);
-    sh.lds_bytes = (uint32_t)d.lds;
+    sh.lds_bytes = (uint32_t)lds;
     sh.resident = cap;
     sh.units = ntiles;
     sh.units_per_step = per;
     // the loop hands out runs of `tiles` tiles to grid x workers workers in turn
-    const uint32_t runs = ceil_div(ntiles, (uint32_t)d.tiles);
+    const uint32_t runs = ceil_div(ntiles, tiles);
     const uint32_t workers = sh.grid * workers_per_block(d);
     sh.min_iters = runs / workers;
     sh.max_iters = ceil_div(runs, workers);

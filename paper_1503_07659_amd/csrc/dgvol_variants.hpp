@@ -2,8 +2,8 @@
 // node count: which body moves the data (LDS-staged or chunk-register), how
 // many waves a workgroup has, and how many 16-column tiles one loop iteration
 // takes (per wave for the staged body, per workgroup for the chunk-register
-// body).  Variant 0 of each list is the library's default; the others are
-// the search space of the autotuner (the paper's autotuning use case, here
+// body).  Variant 0 of each list is the library's default (order 5 in FP64:
+// variant 1 up to a size, see auto_variant); the others are the search space of the autotuner (the paper's autotuning use case, here
 // applied to tile shapes).  A variant's index is its position in its list and
 // is part of the ABI (dg_volume_variant, dg_group.variant).
 //
@@ -34,7 +34,7 @@ constexpr int LCLASS_ALL8 = NUM_VCLASSES;
 constexpr int NUM_LCLASSES = NUM_VCLASSES + 1;
 
 constexpr int VB_S = 0;  // DG_BODY_STAGED
-constexpr int VB_C = 1;  // DG_BODY_CHUNKREG
+constexpr int VB_C = 1;  // DG_BODY_CHUNKREG (FP64 56/1, 84/0, 120/0: stored from the accumulators)
 constexpr int VB_L = 2;  // DG_BODY_STAGED_LEAN (FP64, one tile per wave iteration)
 
 // ------------------------------------------------------------------ FP64
