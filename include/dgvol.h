@@ -122,6 +122,14 @@ dg_status dg_volume_adjoint(const double *D, const double *G, const double *u,
                             int64_t K, int32_t Np, int32_t F, void *stream);
 
 /*
+ * The gu of dg_volume_adjoint alone, for callers with no use for gG (the mesh
+ * and the matrices held fixed): neither u nor D_a u is needed.
+ * Source: as dg_volume_adjoint.  Errors as for dg_volume.
+ */
+dg_status dg_volume_adjoint_u(const double *D, const double *G, const double *gout, double *gu,
+                              int64_t K, int32_t Np, int32_t F, void *stream);
+
+/*
  * Cotangent of the reference differentiation matrices D, FP64.  The forward
  * map is linear in D; for the cotangent gout of out it is the sum over all
  * element columns (k, f)

@@ -21,8 +21,6 @@
 
 namespace dgvol {
 
-constexpr int ADJ_WPB = 8;
-
 // body ids (DG_BODY_STAGED, DG_BODY_CHUNKREG in dgvol.h)
 constexpr int BODY_STAGED = DG_BODY_STAGED;
 constexpr int BODY_CHUNKREG = DG_BODY_CHUNKREG;

@@ -282,9 +282,19 @@ struct AdjPlan {
   uint32_t resident[2];
   uint32_t units[2];     // work units of each kernel
   uint32_t workers[2];   // loop workers per workgroup (waves, or the workgroup itself)
+  uint32_t nworkers;     // workers with a run (below Np = 84)
   uint32_t min_it[2];    // loop iterations of the least and the most loaded worker
   uint32_t max_it[2];
 };
+
+// Grid and workers (waves with a run of tiles) of an adjoint kernel below Np =
+// 84 with `cap` resident workgroups: one worker per tile while there are waves
+// for them, in as many workgroups as tiles (at order 5, 335 tiles, one 8-wave
+// workgroup per 8 tiles used 42 of 256 CUs).
+static void adj_workers(uint32_t tiles, uint32_t cap, uint32_t wpb, uint32_t* grid, uint32_t* workers) {
+  *grid = std::min<uint32_t>(tiles, cap);
+  *workers = std::min<uint32_t>(tiles, *grid * wpb);
+}
 
 template <int NP>
 static dg_status adj_plan(int64_t K, int32_t F, AdjPlan* pl) {
@@ -312,17 +322,16 @@ static dg_status adj_plan(int64_t K, int32_t F, AdjPlan* pl) {
     pl->max_it[1] = (uint32_t)ceil_div(ceil_div((uint64_t)K, nw) * (uint64_t)F, 16);
   } else {
     pl->nk = 1;
-    pl->block[0] = pl->block[1] = WAVE * ADJ_WPB;
-    pl->fn[0] = reinterpret_cast<const void*>(adj_f64_staged_kernel<NP, ADJ_WPB>);
+    pl->block[0] = pl->block[1] = WAVE * adj_wpb(NP, true);
+    pl->fn[0] = reinterpret_cast<const void*>(adj_f64_kernel<NP, adj_wpb(NP, true), true>);
     const int cap = resident_blocks_fn(pl->fn[0], pl->block[0], -1, &err);
     if (err != DG_OK) return err;
     pl->resident[0] = (uint32_t)cap;
-    pl->workers[0] = ADJ_WPB;
+    pl->workers[0] = adj_wpb(NP, true);
     // runs of whole elements per wave, taken as 16-column tiles
-    const uint32_t tiles = ceil_div((uint64_t)K * (uint64_t)F, 16);
-    pl->units[0] = tiles;
-    pl->grid[0] = std::min<uint32_t>(ceil_div(tiles, ADJ_WPB), (uint32_t)cap);
-    const uint64_t nw = (uint64_t)pl->grid[0] * ADJ_WPB;
+    pl->units[0] = ceil_div((uint64_t)K * (uint64_t)F, 16);
+    adj_workers(pl->units[0], (uint32_t)cap, adj_wpb(NP, true), &pl->grid[0], &pl->nworkers);
+    const uint64_t nw = pl->nworkers;
     pl->min_it[0] = (uint32_t)ceil_div((uint64_t)(K / nw) * (uint64_t)F, 16);
     pl->max_it[0] = (uint32_t)ceil_div(ceil_div((uint64_t)K, nw) * (uint64_t)F, 16);
   }
@@ -343,8 +352,32 @@ static dg_status launch_adj_f64(const double* D, const double* G, const double* 
     hipLaunchKernelGGL(adjcr_gG_kernel<NP>, dim3(pl.grid[1]), dim3(pl.block[1]), 0, stream, D, u, gout, gG, (uint32_t)K,
                        (uint32_t)F, (int64_t)ncols * NP);
   } else {
-    hipLaunchKernelGGL((adj_f64_staged_kernel<NP, ADJ_WPB>), dim3(pl.grid[0]), dim3(pl.block[0]), 0, stream, D, G, u,
-                       gout, gu, gG, (uint32_t)K, (uint32_t)F, (int64_t)K * F * NP);
+    hipLaunchKernelGGL((adj_f64_kernel<NP, adj_wpb(NP, true), true>), dim3(pl.grid[0]), dim3(pl.block[0]), 0, stream, D, G, u,
+                       gout, gu, gG, (uint32_t)K, (uint32_t)F, (int64_t)K * F * NP, pl.nworkers);
+  }
+  return hipGetLastError() == hipSuccess ? DG_OK : DG_ELAUNCH;
+}
+
+// gu alone: the gu pass from Np = 84, the kernel without the gG half below.
+template <int NP>
+static dg_status launch_adj_u_f64(const double* D, const double* G, const double* gout, double* gu, int64_t K,
+                                  int32_t F, hipStream_t stream) {
+  int err = DG_OK;
+  const uint64_t ncols = (uint64_t)K * (uint64_t)F;
+  const uint32_t tiles = ceil_div(ncols, 16);
+  if constexpr (NP >= 84) {
+    const int cap = resident_blocks(adjcr_gu_kernel<NP>, WAVE * ADJCR_WPB, -1, &err);
+    if (err != DG_OK) return err;
+    hipLaunchKernelGGL(adjcr_gu_kernel<NP>, dim3(std::min<uint32_t>(tiles, (uint32_t)cap)), dim3(WAVE * ADJCR_WPB), 0,
+                       stream, D, G, gout, gu, (uint32_t)ncols, (uint32_t)F, (int64_t)ncols * NP, tiles);
+  } else {
+    const int cap = resident_blocks(adj_f64_kernel<NP, adj_wpb(NP, false), false>, WAVE * adj_wpb(NP, false), -1, &err);
+    if (err != DG_OK) return err;
+    uint32_t grid, workers;
+    adj_workers(tiles, (uint32_t)cap, adj_wpb(NP, false), &grid, &workers);
+    hipLaunchKernelGGL((adj_f64_kernel<NP, adj_wpb(NP, false), false>), dim3(grid), dim3(WAVE * adj_wpb(NP, false)), 0,
+                       stream, D, G, (const double*)nullptr, gout, gu, (double*)nullptr, (uint32_t)K, (uint32_t)F,
+                       (int64_t)ncols * NP, workers);
   }
   return hipGetLastError() == hipSuccess ? DG_OK : DG_ELAUNCH;
 }
@@ -528,6 +561,16 @@ dg_status dg_volume_adjoint(const double* D, const double* G, const double* u, c
       !aligned(gG, 8))
     return DG_EINVAL;
   DGVOL_DISPATCH(launch_adj_f64, D, G, u, gout, gu, gG, K, F, (hipStream_t)stream)
+}
+
+dg_status dg_volume_adjoint_u(const double* D, const double* G, const double* gout, double* gu, int64_t K, int32_t Np,
+                              int32_t F, void* stream) {
+  bool noop = false;
+  const dg_status st = check_common(K, Np, F, &noop);
+  if (st != DG_OK || noop) return st;
+  if (!D || !G || !gout || !gu) return DG_EINVAL;
+  if (!aligned(D, 8) || !aligned(G, 8) || !aligned(gout, 8) || !aligned(gu, 8)) return DG_EINVAL;
+  DGVOL_DISPATCH(launch_adj_u_f64, D, G, gout, gu, K, F, (hipStream_t)stream)
 }
 
 dg_status dg_volume_grad_d_workspace(int64_t K, int32_t Np, int32_t F, uint64_t* bytes) {

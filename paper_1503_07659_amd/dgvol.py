@@ -99,6 +99,8 @@ def load_library(path=None):
     lib.dg_volume.restype = I32
     lib.dg_volume_adjoint.argtypes = [P, P, P, P, P, P, I64, I32, I32, P]
     lib.dg_volume_adjoint.restype = I32
+    lib.dg_volume_adjoint_u.argtypes = [P, P, P, P, I64, I32, I32, P]
+    lib.dg_volume_adjoint_u.restype = I32
     lib.dg_volume_grad_d.argtypes = [P, P, P, P, P, ctypes.c_uint64, I64, I32, I32, P]
     lib.dg_volume_grad_d.restype = I32
     lib.dg_volume_grad_d_noalloc.argtypes = [P, P, P, P, I64, I32, I32, P]
@@ -203,6 +205,25 @@ def dg_volume_adjoint(D, G, u, gout, gu=None, gG=None):
                                               gu.data_ptr(), gG.data_ptr(), K, Np, F, _stream_handle(dev))
     _raise_on(st, "dg_volume_adjoint")
     return gu, gG
+
+
+def dg_volume_adjoint_u(D, G, gout, gu=None):
+    """FP64 adjoint w.r.t. u alone for the cotangent gout (3, K, F, Np); returns gu (K, F, Np)."""
+    if gout.dim() != 4:
+        raise ValueError(f"gout must be (3, K, F, Np), got shape {tuple(gout.shape)}")
+    K, F, Np = _sizes(gout[0])
+    dev = gout.device
+    _check_tensor("gout", gout, torch.float64, (3, K, F, Np))
+    _check_tensor("D", D, torch.float64, (3, Np, Np), dev)
+    _check_tensor("G", G, torch.float64, (K, 9), dev)
+    if gu is None:
+        gu = torch.empty((K, F, Np), dtype=torch.float64, device=dev)
+    _check_tensor("gu", gu, torch.float64, (K, F, Np), dev)
+    with torch.cuda.device(dev):
+        st = load_library().dg_volume_adjoint_u(D.data_ptr(), G.data_ptr(), gout.data_ptr(), gu.data_ptr(),
+                                                K, Np, F, _stream_handle(dev))
+    _raise_on(st, "dg_volume_adjoint_u")
+    return gu
 
 
 def grad_d_workspace_bytes(K, Np, F):
@@ -442,8 +463,10 @@ class DGVolume(torch.autograd.Function):
         u, G, D = ctx.saved_tensors
         gout = gout.contiguous()
         gu = gG = gD = None
-        if ctx.needs_input_grad[0] or ctx.needs_input_grad[1]:
+        if ctx.needs_input_grad[1]:
             gu, gG = dg_volume_adjoint(D, G, u, gout)
+        elif ctx.needs_input_grad[0]:
+            gu = dg_volume_adjoint_u(D, G, gout)
         if ctx.needs_input_grad[2]:
             gD = dg_volume_grad_d(G, u, gout)
         return (gu if ctx.needs_input_grad[0] else None,
