@@ -65,6 +65,26 @@ constexpr int fwd_f64_staged_lds() {
   return align16(fwd_table_doubles<NP>() * 8) + WPB * staged_wave_doubles<NP, TPI>() * 8;
 }
 
+// First run of tiles of a wave (then every nblk WPB-th).  With a run for every
+// wave the waves of a workgroup take neighbouring runs; with fewer, the runs
+// are dealt to the workgroups first, so that they spread over the CUs.
+template <int WPB>
+__device__ __forceinline__ uint32_t staged_worker(uint32_t bid, uint32_t nblk, uint32_t wave, uint32_t nrun) {
+  return nrun >= nblk * WPB ? bid * WPB + wave : wave * nblk + bid;
+}
+
+// The A-operand table of a staged body.  The callers request their first tile
+// before it, so that the two latencies overlap (a fifth of a small launch).
+template <int NP, int WPB>
+__device__ __forceinline__ void build_fwd_table(const double* __restrict__ D, double* afr) {
+  using Sh = Shape<NP>;
+  for (int e = threadIdx.x; e < fwd_table_doubles<NP>(); e += WAVE * WPB) {
+    const int ts = e >> 6;
+    afr[e] = afrag_f64<NP>(D, ts / Sh::KS64, ts % Sh::KS64, e & 63);
+  }
+  __syncthreads();
+}
+
 // LEAN: the register-lean form (two 8-wave workgroups per CU, at most 128
 // registers a lane): each A operand is read from LDS right before its product
 // instead of one k-step ahead, and the geometric factors are read after the
@@ -82,11 +102,6 @@ __device__ __forceinline__ void fwd_f64_staged_single(const FwdArgs<double>& p, 
   constexpr int NRAW = (TILE + WAVE - 1) / WAVE;
   double* afr = reinterpret_cast<double*>(lds);
   double* stg_all = reinterpret_cast<double*>(lds + align16(NFRAG * 8));
-  for (int e = threadIdx.x; e < NFRAG; e += WAVE * WPB) {
-    const int ts = e >> 6;
-    afr[e] = afrag_f64<NP>(p.D, ts / Sh::KS64, ts % Sh::KS64, e & 63);
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g = lane >> 4;
   // wave-uniform (readfirstlane): branches on it are scalar (measured: order 4
@@ -95,7 +110,7 @@ __device__ __forceinline__ void fwd_f64_staged_single(const FwdArgs<double>& p, 
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double* stg = stg_all + wave * TILE;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = bid * WPB + wave;
+  uint32_t t = staged_worker<WPB>(bid, nblk, wave, p.ntiles);
   double raw[NRAW];
   auto load_raw = [&](uint32_t tt) {
     const double* __restrict__ src = p.u + (int64_t)tt * TILE;
@@ -107,6 +122,7 @@ __device__ __forceinline__ void fwd_f64_staged_single(const FwdArgs<double>& p, 
     }
   };
   if (t < p.ntiles) load_raw(t);
+  build_fwd_table<NP, WPB>(p.D, afr);
   for (; t < p.ntiles; t += stride) {
     const uint32_t col0 = t * 16;
     const int cnt = (int)min(16u, p.ncols - col0) * NP;
@@ -208,18 +224,13 @@ __device__ __forceinline__ void fwd_f64_staged_early(const FwdArgs<double>& p, u
   constexpr int LD = NP + 1;
   double* afr = reinterpret_cast<double*>(lds);
   double* stg_all = reinterpret_cast<double*>(lds + align16(NFRAG * 8));
-  for (int e = threadIdx.x; e < NFRAG; e += WAVE * WPB) {
-    const int ts = e >> 6;
-    afr[e] = afrag_f64<NP>(p.D, ts / Sh::KS64, ts % Sh::KS64, e & 63);
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g = lane >> 4;
   // wave-uniform for certain: the buffer descriptors are built from it
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double* stg = stg_all + wave * 16 * LD;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = bid * WPB + wave;
+  uint32_t t = staged_worker<WPB>(bid, nblk, wave, p.ntiles);
   double raw[NRAW];
   // tile tt's u through a buffer range of its valid words; past the last tile
   // the range is empty (zeros, no memory access)
@@ -239,6 +250,7 @@ __device__ __forceinline__ void fwd_f64_staged_early(const FwdArgs<double>& p, u
     wave_sync();
   };
   load_raw(t);
+  build_fwd_table<NP, WPB>(p.D, afr);
   stage();
   for (; t < p.ntiles; t += stride) {
     const uint32_t col0 = t * 16;
@@ -325,11 +337,6 @@ __device__ __forceinline__ void fwd_f64_staged_multi(const FwdArgs<double>& p, u
   constexpr int GW = TPI * 16 * 9;                 // G words of at most 16 TPI elements
   constexpr int NGR = (GW + WAVE - 1) / WAVE;
   double* afr = reinterpret_cast<double*>(lds);
-  for (int e = threadIdx.x; e < NFRAG; e += WAVE * WPB) {
-    const int ts = e >> 6;
-    afr[e] = afrag_f64<NP>(p.D, ts / Sh::KS64, ts % Sh::KS64, e & 63);
-  }
-  __syncthreads();
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g = lane >> 4;
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -337,7 +344,7 @@ __device__ __forceinline__ void fwd_f64_staged_multi(const FwdArgs<double>& p, u
   double* sg = su + RUN;
   const uint32_t nrun = (p.ntiles + TPI - 1) / TPI;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = bid * WPB + wave;
+  uint32_t t = staged_worker<WPB>(bid, nblk, wave, nrun);
   double raw[NRAW], graw[NGR];
   // first element of the run and the number of its G words
   auto run_elems = [&](uint32_t tt, uint32_t& e0, int& ng) __attribute__((always_inline)) {
@@ -376,6 +383,7 @@ __device__ __forceinline__ void fwd_f64_staged_multi(const FwdArgs<double>& p, u
     wave_sync();
   };
   load_run(t);
+  build_fwd_table<NP, WPB>(p.D, afr);
   stage();
   for (; t < nrun; t += stride) {
     const uint32_t col0 = t * (16 * TPI);

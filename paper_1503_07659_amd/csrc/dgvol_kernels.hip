@@ -226,12 +226,14 @@ static inline int launch_class(const VariantDesc& d, bool by_class) {
   return d.wpb == 8 ? LCLASS_ALL8 : VCLASS_WAVE4;
 }
 
-// Persistent grid of a single-group launch of variant d over `ntiles` tiles.
+// Persistent grid of a single-group launch of variant d over `ntiles` tiles: a
+// workgroup per loop step's tiles of one worker, up to the resident count (a
+// small problem's runs of tiles then sit on as many CUs as there are runs).
 static uint32_t single_grid(const VariantDesc& d, uint32_t ntiles, int* err, uint32_t* resident) {
   const int cap = resident_blocks_fn(d.fn, WAVE * d.wpb1, d.lds1, err);
   if (*err != DG_OK) return 0;
   if (resident) *resident = (uint32_t)cap;
-  return std::min<uint32_t>(ceil_div(ntiles, units_per_step1(d)), (uint32_t)cap);
+  return std::min<uint32_t>(ceil_div(ntiles, (uint32_t)d.tiles1), (uint32_t)cap);
 }
 
 template <typename T>
@@ -746,7 +748,7 @@ dg_status dg_launch_shape_query(int32_t op, int32_t form, int32_t Np, int32_t va
       cap = (uint32_t)resident_blocks_fn(batched_fn(form, lc), sh.block, d.lds, &err);
     }
     if (err != DG_OK) return err;
-    sh.grid = std::min<uint32_t>(ceil_div(ntiles, per), cap);
+    sh.grid = std::min<uint32_t>(ceil_div(ntiles, single ? tiles : per), cap);
     sh.lds_bytes = (uint32_t)lds;
     sh.resident = cap;
     sh.units = ntiles;
