@@ -694,19 +694,20 @@ dg_status dg_volume_batched(const dg_group* groups, int32_t ngroups, int32_t F, 
     // and left a small group (order 6 of the mixed batch) one workgroup short:
     // it then finished last.
     uint32_t nb[DG_MAX_GROUPS];
-    uint32_t used = 0;
+    double load[DG_MAX_GROUPS];
+    uint32_t used = (uint32_t)ng;
     for (int i = 0; i < ng; ++i) {
       nb[i] = 1;
-      ++used;
+      load[i] = step_cost[i] * (double)steps[i];
     }
-    auto load = [&](int i) { return step_cost[i] * (double)ceil_div(steps[i], nb[i]); };
     while (used < (uint32_t)cap) {
       int pick = -1;
       for (int i = 0; i < ng; ++i)
-        if (nb[i] < max_blocks[i] && (pick < 0 || load(i) > load(pick))) pick = i;
+        if (nb[i] < max_blocks[i] && (pick < 0 || load[i] > load[pick])) pick = i;
       if (pick < 0) break;
       ++nb[pick];
       ++used;
+      load[pick] = step_cost[pick] * (double)ceil_div(steps[pick], nb[pick]);
     }
     uint32_t begin = 0;
     for (int i = 0; i < ng; ++i) {

@@ -141,11 +141,22 @@ def _raise_on(status, what):
         raise DGVolError(status, f"{what}: {strerror(status)}")
 
 
-def _stream_handle(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _call(fn, what, dev, *args):
+    """Run a library entry point on `dev` (the device of a checked tensor) and torch's current stream of it."""
+    if torch.cuda.current_device() == dev.index:
+        st = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+    else:
+        with torch.cuda.device(dev):
+            st = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+    if st != DG_OK:
+        _raise_on(st, what)
 
 
 def _check_tensor(name, t, dtype, shape, device=None):
+    # the accepted case in one expression; what follows says what is wrong
+    if isinstance(t, torch.Tensor) and t.dtype is dtype and t.is_cuda and t.shape == shape and t.is_contiguous() \
+            and (device is None or t.device == device):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.dtype != dtype:
@@ -177,12 +188,11 @@ def dg_volume(D, G, u, out=None):
     _check_tensor("D", D, torch.float64, (3, Np, Np), dev)
     _check_tensor("G", G, torch.float64, (K, 9), dev)
     if out is None:
-        out = torch.empty((3, K, F, Np), dtype=torch.float64, device=dev)
-    _check_tensor("out", out, torch.float64, (3, K, F, Np), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume(D.data_ptr(), G.data_ptr(), u.data_ptr(), out.data_ptr(),
-                                      K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume")
+        out = u.new_empty((3, K, F, Np))
+    else:
+        _check_tensor("out", out, torch.float64, (3, K, F, Np), dev)
+    _call(load_library().dg_volume, "dg_volume", dev, D.data_ptr(), G.data_ptr(), u.data_ptr(), out.data_ptr(),
+          K, Np, F)
     return out
 
 
@@ -195,15 +205,15 @@ def dg_volume_adjoint(D, G, u, gout, gu=None, gG=None):
     _check_tensor("G", G, torch.float64, (K, 9), dev)
     _check_tensor("gout", gout, torch.float64, (3, K, F, Np), dev)
     if gu is None:
-        gu = torch.empty((K, F, Np), dtype=torch.float64, device=dev)
+        gu = u.new_empty((K, F, Np))
+    else:
+        _check_tensor("gu", gu, torch.float64, (K, F, Np), dev)
     if gG is None:
-        gG = torch.empty((K, 9), dtype=torch.float64, device=dev)
-    _check_tensor("gu", gu, torch.float64, (K, F, Np), dev)
-    _check_tensor("gG", gG, torch.float64, (K, 9), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume_adjoint(D.data_ptr(), G.data_ptr(), u.data_ptr(), gout.data_ptr(),
-                                              gu.data_ptr(), gG.data_ptr(), K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume_adjoint")
+        gG = u.new_empty((K, 9))
+    else:
+        _check_tensor("gG", gG, torch.float64, (K, 9), dev)
+    _call(load_library().dg_volume_adjoint, "dg_volume_adjoint", dev, D.data_ptr(), G.data_ptr(), u.data_ptr(),
+          gout.data_ptr(), gu.data_ptr(), gG.data_ptr(), K, Np, F)
     return gu, gG
 
 
@@ -211,18 +221,19 @@ def dg_volume_adjoint_u(D, G, gout, gu=None):
     """FP64 adjoint w.r.t. u alone for the cotangent gout (3, K, F, Np); returns gu (K, F, Np)."""
     if gout.dim() != 4:
         raise ValueError(f"gout must be (3, K, F, Np), got shape {tuple(gout.shape)}")
-    K, F, Np = _sizes(gout[0])
+    K, F, Np = gout.shape[1:]
+    if Np not in SUPPORTED_NP:
+        raise ValueError(f"unsupported node count Np={Np}; supported: {SUPPORTED_NP}")
     dev = gout.device
     _check_tensor("gout", gout, torch.float64, (3, K, F, Np))
     _check_tensor("D", D, torch.float64, (3, Np, Np), dev)
     _check_tensor("G", G, torch.float64, (K, 9), dev)
     if gu is None:
-        gu = torch.empty((K, F, Np), dtype=torch.float64, device=dev)
-    _check_tensor("gu", gu, torch.float64, (K, F, Np), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume_adjoint_u(D.data_ptr(), G.data_ptr(), gout.data_ptr(), gu.data_ptr(),
-                                                K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume_adjoint_u")
+        gu = gout.new_empty((K, F, Np))
+    else:
+        _check_tensor("gu", gu, torch.float64, (K, F, Np), dev)
+    _call(load_library().dg_volume_adjoint_u, "dg_volume_adjoint_u", dev, D.data_ptr(), G.data_ptr(),
+          gout.data_ptr(), gu.data_ptr(), K, Np, F)
     return gu
 
 
@@ -253,10 +264,8 @@ def dg_volume_grad_d(G, u, gout, gD=None, work=None):
     if not isinstance(work, torch.Tensor) or work.device != dev or not work.is_contiguous():
         raise ValueError("work must be a contiguous tensor on the device of u")
     nbytes = work.numel() * work.element_size()
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume_grad_d(G.data_ptr(), u.data_ptr(), gout.data_ptr(), gD.data_ptr(),
-                                             work.data_ptr(), nbytes, K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume_grad_d")
+    _call(load_library().dg_volume_grad_d, "dg_volume_grad_d", dev, G.data_ptr(), u.data_ptr(),
+          gout.data_ptr(), gD.data_ptr(), work.data_ptr(), nbytes, K, Np, F)
     return gD
 
 
@@ -271,10 +280,8 @@ def dg_volume_grad_d_noalloc(G, u, gout, gD):
     _check_tensor("G", G, torch.float64, (K, 9), dev)
     _check_tensor("gout", gout, torch.float64, (3, K, F, Np), dev)
     _check_tensor("gD", gD, torch.float64, (3, Np, Np), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume_grad_d_noalloc(G.data_ptr(), u.data_ptr(), gout.data_ptr(), gD.data_ptr(),
-                                                     K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume_grad_d_noalloc")
+    _call(load_library().dg_volume_grad_d_noalloc, "dg_volume_grad_d_noalloc", dev, G.data_ptr(), u.data_ptr(),
+          gout.data_ptr(), gD.data_ptr(), K, Np, F)
     return gD
 
 
@@ -286,12 +293,11 @@ def dg_volume_f32s(D, G, u, out=None):
     _check_tensor("D", D, torch.float32, (3, Np, Np), dev)
     _check_tensor("G", G, torch.float32, (K, 9), dev)
     if out is None:
-        out = torch.empty((3, K, F, Np), dtype=torch.float32, device=dev)
-    _check_tensor("out", out, torch.float32, (3, K, F, Np), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume_f32s(D.data_ptr(), G.data_ptr(), u.data_ptr(), out.data_ptr(),
-                                           K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume_f32s")
+        out = u.new_empty((3, K, F, Np))
+    else:
+        _check_tensor("out", out, torch.float32, (3, K, F, Np), dev)
+    _call(load_library().dg_volume_f32s, "dg_volume_f32s", dev, D.data_ptr(), G.data_ptr(), u.data_ptr(),
+          out.data_ptr(), K, Np, F)
     return out
 
 
@@ -307,10 +313,8 @@ def dg_volume_variant(form, variant, D, G, u, out=None):
     if out is None:
         out = torch.empty((3, K, F, Np), dtype=dtype, device=dev)
     _check_tensor("out", out, dtype, (3, K, F, Np), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_volume_variant(int(form), int(variant), D.data_ptr(), G.data_ptr(), u.data_ptr(),
-                                              out.data_ptr(), K, Np, F, _stream_handle(dev))
-    _raise_on(st, "dg_volume_variant")
+    _call(load_library().dg_volume_variant, "dg_volume_variant", dev, int(form), int(variant), D.data_ptr(),
+          G.data_ptr(), u.data_ptr(), out.data_ptr(), K, Np, F)
     return out
 
 
@@ -353,8 +357,7 @@ def dg_volume_batched(groups, form=FORM_F64, outs=None, variants=None, costs=Non
         return []
     F = groups[0][2].shape[1] if groups[0][2].dim() == 3 else None
     dev = groups[0][2].device
-    arr = (DgGroup * max(1, len(groups)))()
-    res = []
+    table, res = [], []
     for gi, (D, G, u) in enumerate(groups):
         K, Fg, Np = _sizes(u)
         if Fg != F:
@@ -362,18 +365,17 @@ def dg_volume_batched(groups, form=FORM_F64, outs=None, variants=None, costs=Non
         _check_tensor("u", u, dtype, (K, F, Np), dev)
         _check_tensor("D", D, dtype, (3, Np, Np), dev)
         _check_tensor("G", G, dtype, (K, 9), dev)
-        out = outs[gi] if outs is not None else torch.empty((3, K, F, Np), dtype=dtype, device=dev)
-        _check_tensor("out", out, dtype, (3, K, F, Np), dev)
+        if outs is None:
+            out = u.new_empty((3, K, F, Np))
+        else:
+            out = outs[gi]
+            _check_tensor("out", out, dtype, (3, K, F, Np), dev)
         res.append(out)
-        arr[gi].Np = Np
-        arr[gi].variant = VARIANT_AUTO if variants is None else int(variants[gi])
-        arr[gi].K = K
-        arr[gi].D, arr[gi].G, arr[gi].u, arr[gi].out = D.data_ptr(), G.data_ptr(), u.data_ptr(), out.data_ptr()
-        arr[gi].cost = 0.0 if costs is None else float(costs[gi])
-    with torch.cuda.device(dev):
-        flags = int(form) | (BATCH_BY_CLASS if by_class else 0)
-        st = load_library().dg_volume_batched(arr, len(groups), int(F), flags, _stream_handle(dev))
-    _raise_on(st, "dg_volume_batched")
+        table.append(DgGroup(Np, VARIANT_AUTO if variants is None else int(variants[gi]), K, D.data_ptr(),
+                             G.data_ptr(), u.data_ptr(), out.data_ptr(), 0.0 if costs is None else float(costs[gi])))
+    flags = int(form) | (BATCH_BY_CLASS if by_class else 0)
+    _call(load_library().dg_volume_batched, "dg_volume_batched", dev, (DgGroup * len(table))(*table), len(table),
+          int(F), flags)
     return res
 
 
@@ -383,9 +385,8 @@ def dg_stream_calibrate(src, dst, copies):
     dev = src.device
     _check_tensor("src", src, torch.float64, (n,))
     _check_tensor("dst", dst, torch.float64, (copies * n,), dev)
-    with torch.cuda.device(dev):
-        st = load_library().dg_stream_calibrate(src.data_ptr(), dst.data_ptr(), n, copies, _stream_handle(dev))
-    _raise_on(st, "dg_stream_calibrate")
+    _call(load_library().dg_stream_calibrate, "dg_stream_calibrate", dev, src.data_ptr(), dst.data_ptr(), n,
+          copies)
     return dst
 
 
@@ -407,10 +408,8 @@ def dg_stream_calibrate_tiles(src, dst, tiles_per_wave):
     ntiles = src.numel() // TILE_STREAM_WORDS
     if dst.numel() != 3 * src.numel():
         raise ValueError("dst must hold three planes of src's size")
-    with torch.cuda.device(src.device):
-        st = load_library().dg_stream_calibrate_tiles(src.data_ptr(), dst.data_ptr(), ntiles, int(tiles_per_wave),
-                                                      _stream_handle(src.device))
-    _raise_on(st, "dg_stream_calibrate_tiles")
+    _call(load_library().dg_stream_calibrate_tiles, "dg_stream_calibrate_tiles", src.device, src.data_ptr(),
+          dst.data_ptr(), ntiles, int(tiles_per_wave))
 
 
 def dg_mfma_calibrate(iters, sink=None):
@@ -419,9 +418,7 @@ def dg_mfma_calibrate(iters, sink=None):
     if sink is None:
         sink = torch.empty(MFMA_CAL_BLOCKS * 256, dtype=torch.float64, device=dev)
     _check_tensor("sink", sink, torch.float64, (MFMA_CAL_BLOCKS * 256,))
-    with torch.cuda.device(sink.device):
-        st = load_library().dg_mfma_calibrate(sink.data_ptr(), int(iters), _stream_handle(sink.device))
-    _raise_on(st, "dg_mfma_calibrate")
+    _call(load_library().dg_mfma_calibrate, "dg_mfma_calibrate", sink.device, sink.data_ptr(), int(iters))
     return sink, MFMA_CAL_BLOCKS * 4 * int(iters) * 4 * 2048
 
 
@@ -436,10 +433,8 @@ def dg_mfma_calibrate_beside(iters, viters, mode, sink=None):
     if sink is None:
         sink = torch.empty(MFMA_BESIDE_BLOCKS * 512, dtype=torch.float64, device=dev)
     _check_tensor("sink", sink, torch.float64, (MFMA_BESIDE_BLOCKS * 512,))
-    with torch.cuda.device(sink.device):
-        st = load_library().dg_mfma_calibrate_beside(sink.data_ptr(), int(iters), int(viters), int(mode),
-                                                     _stream_handle(sink.device))
-    _raise_on(st, "dg_mfma_calibrate_beside")
+    _call(load_library().dg_mfma_calibrate_beside, "dg_mfma_calibrate_beside", sink.device, sink.data_ptr(),
+          int(iters), int(viters), int(mode))
     return sink
 
 
