@@ -14,14 +14,11 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 // The value of lane M of each row of 16 lanes, in every lane of that row
-// (DPP row_newbcast on each 32-bit half).  Every lane of the wave must be active.
+// (DPP row_newbcast, which moves 64 bits at once).  Every lane of the wave must be active.
 template <int M>
 __device__ __forceinline__ double row_bcast_f64(double v) {
   static_assert(M >= 0 && M < 16, "lane within a row");
-  const unsigned long long b = __builtin_bit_cast(unsigned long long, v);
-  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned int)b, 0x150 + M, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned int)(b >> 32), 0x150 + M, 0xf, 0xf, false);
-  return __builtin_bit_cast(double, ((unsigned long long)(unsigned int)hi << 32) | (unsigned int)lo);
+  return __builtin_amdgcn_update_dpp(0.0, v, 0x150 + M, 0xf, 0xf, true);
 }
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -34,6 +31,13 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Keeps values derived from x from being hoisted out of a loop (they would
+// hold registers through the products).
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
 // ------------------------------------------------------------------ FP64 A operands
@@ -74,6 +78,16 @@ __device__ __forceinline__ int tswz(int lane, int s) { return lane ^ ((s & 3) <<
 // (1:3 read:write stream +2 %, split-BF16 forward 10-16 %).
 template <class T>
 __device__ __forceinline__ void store_stream(T* p, const T& v) { __builtin_nontemporal_store(v, p); }
+
+// Columns of [c0, c0 + most) below ncols.  Written as c0 < ncols ? min(most,
+// ncols - c0) : 0, a second such expression with another c0 in the same
+// function let the compiler fold this one to `most` (it takes a no-wrap flag
+// of the guarded subtraction for a fact), and the loads then ran past the
+// arrays.  (A signed clamp to [0, most] becomes a vector median, and every
+// buffer access built from it a loop over the lanes' descriptors.)
+__device__ __forceinline__ uint32_t cols_left(uint32_t ncols, uint32_t c0, uint32_t most) {
+  return min(ncols, c0 + most) - min(ncols, c0);
+}
 
 // Raw buffer access: loads past the descriptor's byte range return zero and
 // stores past it are dropped by the hardware range check, so a wave can issue

@@ -105,13 +105,6 @@ constexpr int fwd_f64_direct_lds() {
   return (2 * T::U + T::S::NGB * T::G + 2 * T::X + T::DL) * 8;
 }
 
-// Keeps values derived from x from being hoisted out of a loop (they would
-// hold registers through the products).
-__device__ __forceinline__ int opaque(int x) {
-  asm volatile("" : "+v"(x));
-  return x;
-}
-
 template <int NP, int WPB, int TILES>
 __device__ __forceinline__ void fwd_f64_direct_body(const FwdArgs<double>& p, uint32_t bid, uint32_t nblk, char* lds) {
   using S = DirectShape<NP, WPB>;
@@ -216,7 +209,7 @@ __device__ __forceinline__ void fwd_f64_direct_body(const FwdArgs<double>& p, ui
     for (int b = 0; b < 3; ++b) buffer_store_f64(ro[b], off, gk[b] * r + gk[3 + b] * s + gk[6 + b] * t);
   };
   auto planes = [&](__amdgpu_buffer_rsrc_t (&ro)[3], uint32_t c0) __attribute__((always_inline)) {
-    const uint32_t ncl = c0 < p.ncols ? min(16u, p.ncols - c0) : 0u;
+    const uint32_t ncl = cols_left(p.ncols, c0, 16);
 #pragma unroll
     for (int b = 0; b < 3; ++b) ro[b] = buffer_range(p.out + b * p.plane + (int64_t)c0 * NP, ncl * NP * 8u);
   };

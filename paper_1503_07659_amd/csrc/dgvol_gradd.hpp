@@ -4,31 +4,42 @@
 // planes the cotangent of D is a sum over every element column c = (k, f):
 //   W_a[c][i]   = sum_b G[k][3a+b] gout[b][c][i]
 //   gD[a][i][j] = sum_c W_a[c][i] u[c][j]
-// Stacking the three directions, rows r = a Np + i, this is ONE contraction
-//   gD[r][j] = sum_c W[c][r] u[c][j]          ([3Np x ncols] . [ncols x Np])
-// whose reduction dimension is the (long) column axis.  It runs on the FP64
-// matrix cores with the columns as the MFMA k dimension:
+// i.e. per direction one contraction [Np x ncols] . [ncols x Np] whose
+// reduction runs over the (long) column axis.  It runs on the FP64 matrix
+// cores with the columns as the MFMA k dimension, four per k-step:
 //
-//   * the 3Np stacked rows form ceil(3Np/16) row tiles and the Np columns
-//     ceil(Np/16) column blocks (stacking wastes less of a 16-row tile than
-//     padding every direction separately);
-//   * the columns are split into npart contiguous ranges; one workgroup owns
-//     one range (at the two highest orders NSPLIT workgroups, each with a
-//     share of the row tiles) and keeps its output tiles in accumulators
-//     spread over its waves; with fewer tiles than waves the waves also split
-//     the k steps and add their partial tiles at the end in a fixed order;
-//   * per step the workgroup stages u[c][:] and W[c][rows] in LDS, row-major
-//     per column; each thread stages a fixed column, so it needs the
-//     geometric factors of one element only;
-//   * the staging is software-pipelined over two LDS buffers: while the waves
-//     multiply step s out of one buffer, each thread writes step s+1 (loaded
-//     into registers during step s-1) into the other and requests step s+2
-//     from memory, with one barrier per step;
-//   * each workgroup writes its partial gD to work[part]; a second kernel adds
-//     the partials in a fixed order.
+//   * lane (n, g) of a wave owns column 4s + g of k-step s and nodes n, 16 + n,
+//     ... of it, loads u and gout there (128-byte runs), forms W in its
+//     registers and feeds both to the products as they are: the A operand of a
+//     16-row tile is W at the lane's node of that tile, the B operand u.
+//     Nothing passes through LDS, and waves meet no barrier until the end;
+//   * the last Np mod 16 nodes do not pad a tile: they are held as quads of 4
+//     (registers Q below) whose products run as v_mfma_f64_4x4x4f64 (four
+//     4 x 4 blocks, 16 cycles against 64 for a 16 x 16 tile);
+//   * loads run two k-steps ahead (u one, each register reloaded right after
+//     its products, where registers are short: Np >= 56); the 9 geometric factors of a column come as
+//     one load (lane n of its 16-lane row takes factor n) and are handed to
+//     the row by DPP broadcasts;
+//   * the waves of a workgroup share its column range; a wave holds every
+//     output (up to Np = 35) or those of a group of rows (Np = 56: 2 groups,
+//     84: 4, 120: 8) in its accumulators.  Groups of rows, not directions:
+//     gout is then read once and only u by every group.  (One workgroup per
+//     direction read everything three times: order 5, K = 2^19 took 1049 us
+//     instead of 632.)  At the end the waves of one group add their accumulators through
+//     LDS in order, and the workgroup writes one partial sum to work[part]; a
+//     second kernel adds the partial sums in a fixed order.
 //
 // The partition depends only on (K, F, Np), never on the device, and every
 // sum runs in a fixed order, so the result is reproducible bit for bit.
+//
+// Bound: the memory up to Np = 35, the FP64 products from 56 (2400 / 5328 /
+// 10848 matrix cycles per 4 columns at Np = 56 / 84 / 120, no padding), with
+// W and the broadcasts beside them (a fifth at Np = 56).  Measured against the
+// kernels it replaced (W and u staged through LDS, one barrier per 16 to 128
+// columns; order 5: producer and consumer waves), F = 3, both kernels of a
+// call: 2e7 nodal values, order 1 177 -> 157 us, 2 191 -> 149, 3 203 -> 140, 4
+// 219 -> 129, 6 305 -> 209, 7 483 -> 281; order 5, K = 2^19 635 -> 632; 3e5
+// values, order 4 17.4 -> 10.9, 5 20 -> 13, 6 29 -> 17, 7 33 -> 25.
 #pragma once
 
 #include <type_traits>
@@ -37,52 +48,54 @@
 
 namespace dgvol {
 
-// Columns per partition unit; every staging step (16..128 columns) divides it.
+// Columns per partial sum, at least (the workspace holds one per GD_UNIT).
 constexpr int GD_UNIT = 128;
-constexpr int GD_WPB = 8;
 
-// Upper bound on the number of partial sums (a function of Np only).
+// Bound on the number of partial sums the workspace holds (a function of Np only).
 __host__ __device__ constexpr uint32_t gd_maxpart(int np) { return np <= 35 ? 1024u : 512u; }
-
-// Row stride in LDS: an odd multiple of 16 doubles, so the 16-lane row
-// segments of an MFMA operand read start 128 bytes apart modulo 256 and two of
-// them never share banks.
-constexpr int gd_ld(int n16) { return (n16 / 16) % 2 == 1 ? n16 : n16 + 16; }
 
 template <int NP>
 struct GdShape {
-  static constexpr int NTH = WAVE * GD_WPB;
-  static constexpr int NB = (NP + 15) / 16;            // column blocks (j)
-  static constexpr int RT = (3 * NP + 15) / 16;        // row tiles (stacked r = a Np + i)
-  static constexpr int NSPLIT = NP >= 120 ? 4 : (NP >= 84 ? 2 : 1);
-  static constexpr int RTS = (RT + NSPLIT - 1) / NSPLIT;  // row tiles per workgroup
-  static constexpr int NTW = RTS * NB;                  // output tiles per workgroup
-  static constexpr int KSPLIT = NTW >= GD_WPB ? 1 : (NTW == 1 ? 8 : (NTW == 2 ? 4 : 2));
-  static constexpr int SLOTS = NTW * KSPLIT;            // (tile, k share) pairs
-  static constexpr int TPW = (SLOTS + GD_WPB - 1) / GD_WPB;
-  // columns per step: two staging buffers of at most 32 KB, so that two
-  // workgroups fit the LDS of a CU
-  static constexpr int CH = NP <= 4 ? 128 : (NP <= 10 ? 64 : (NP <= 35 ? 32 : 16));
-  static constexpr int TPC = NTH / CH;                  // threads staging one column
-  static constexpr int NXU = (NP + TPC - 1) / TPC;      // values per thread and plane
-  static constexpr int LDU = gd_ld(16 * NB);
-  static constexpr int LDW = gd_ld(16 * RTS);
-  static constexpr int STAGE_DOUBLES = CH * (LDU + LDW);  // one staging buffer
-  static constexpr int RED_DOUBLES = KSPLIT > 1 ? SLOTS * 256 : 0;
-  static constexpr int LDS_DOUBLES = 2 * STAGE_DOUBLES > RED_DOUBLES ? 2 * STAGE_DOUBLES : RED_DOUBLES;
-  static_assert(2 * LDS_DOUBLES * 8 <= 160 * 1024, "two workgroups per CU");
-  static_assert(GD_UNIT % CH == 0 && CH % 4 == 0, "staging step");
-  static_assert((CH / 4) % KSPLIT == 0, "k steps split evenly");
-  // directions whose W rows one workgroup holds (its geometric factors in registers)
-  static constexpr int NDIR = NSPLIT > 1 ? 2 : 3;
-  static constexpr bool dirs_fit() {
-    for (int s = 0; s < NSPLIT; ++s) {
-      const int r0 = s * RTS * 16, r1 = (s + 1) * RTS * 16 < 3 * NP ? (s + 1) * RTS * 16 : 3 * NP;
-      if (r0 < r1 && (r1 - 1) / NP - r0 / NP + 1 > NDIR) return false;
-    }
-    return true;
+  // Np = 10: one padded tile; else whole 16-node tiles and up to two quads
+  static constexpr int NF = NP == 10 ? 1 : NP / 16;
+  static constexpr int NQ = NP == 10 ? 0 : (NP % 16 + 3) / 4;
+  static_assert(NQ <= 2, "at most two quads");
+  // Row groups of a workgroup's waves.  Np = 56: tiles 0, 1; tile 2 and the
+  // quads.  Np = 84: tile g and one direction of tile 4 (g < 3), tile 3 and
+  // the quad.  Np = 120: tile g (g < 7), the quads.  A workgroup is 4 waves, or
+  // 8 (two per SIMD) with row groups.  More registers a wave (one per SIMD,
+  // 512) would need fewer groups, but the compiler then moves accumulators
+  // between the two register files around the products: 5 times slower.
+  static constexpr int NRG = NP == 120 ? 8 : NP == 84 ? 4 : NP == 56 ? 2 : 1;
+  static constexpr int WPB = NRG > 1 ? 8 : 4;
+  static constexpr int SLICES = WPB / NRG;       // column slices
+  static constexpr int NTH = WAVE * WPB;
+  // Two kinds of groups: the last one (with the quads) and the others, which
+  // differ by their first tile (and extra direction) only.  First tile of group
+  // g; whole tiles, extra tile or -1, and quads of a kind.
+  __host__ __device__ static constexpr int t0(int g) { return NP == 56 ? 2 * g : g; }
+  static constexpr int nt(bool last) {
+    return NP == 56 ? (last ? 1 : 2) : NP == 84 ? 1 : NP == 120 ? (last ? 0 : 1) : NF;
   }
-  static_assert(dirs_fit(), "a workgroup's rows span at most NDIR directions");
+  static constexpr int xt(bool last) { return NP == 84 && !last ? 4 : -1; }
+  static constexpr bool rq(bool last) { return NQ > 0 && last; }
+  // doubles per lane of a group's accumulators for nd directions
+  static constexpr int acc(bool last, int nd) {
+    return nd * nt(last) * (4 * NF + NQ) + (xt(last) >= 0 ? 4 * NF + NQ : 0) + (rq(last) ? nd * (NQ * NF + NQ) : 0);
+  }
+  // of them, those that pass through LDS at a time (Np = 84: all would be 166 KiB)
+  static constexpr int passes(int nd) { return NP == 84 && nd == 3 ? 2 : 1; }
+  static constexpr int acc_pass(bool last, int nd) { return (acc(last, nd) + passes(nd) - 1) / passes(nd); }
+  static constexpr int lds_group(int nd) {
+    return (acc_pass(true, nd) > acc_pass(false, nd) ? acc_pass(true, nd) : acc_pass(false, nd)) * WAVE;
+  }
+  // (each row group of a workgroup has its own; rs workgroups share the groups)
+  static constexpr int lds_doubles(int nd, int rs) { return SLICES > 1 ? NRG / rs * lds_group(nd) : 1; }
+  // waves per SIMD the registers allow; partial sums: as many as run at once on
+  // 256 CUs (a constant, not read from the device)
+  static constexpr int WPS = NP <= 20 ? 4 : 2;
+  static constexpr uint32_t MAXPART = 256u * 4u * WPS / WPB;
+  static_assert(MAXPART <= gd_maxpart(NP), "the workspace holds every partial sum");
 };
 
 struct GdArgs {
@@ -93,582 +106,418 @@ struct GdArgs {
   uint32_t ncols;    // K * F
   uint32_t F;
   int64_t plane;     // K * F * Np
-  uint32_t nunits;   // ceil(ncols / GD_UNIT)
   uint32_t npart;
 };
 
-// Two workgroups per CU (at most 128 registers a lane) so that one stages
-// while the other multiplies.
-template <int NP>
-__global__ __launch_bounds__(GdShape<NP>::NTH) __attribute__((amdgpu_waves_per_eu(4, 8)))
-void gd_partial_kernel(GdArgs p) {
-  using S = GdShape<NP>;
-  constexpr int CH = S::CH;
-  constexpr int SUB = GD_UNIT / CH;  // steps per partition unit
-  __shared__ double lds[S::LDS_DOUBLES];
-  // staging buffer b: u[c][j] at [b][c][LDU], W[c][r - r0] at [b][CH LDU + c LDW]
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  // Workgroups of one column range sit on one XCD (workgroups are dealt to
-  // the 8 XCDs in turn), so the NSPLIT reads of a column hit one L2.
-  uint32_t part, split;
-  if constexpr (S::NSPLIT == 1) {
-    part = blockIdx.x;
-    split = 0;
-  } else {
-    const uint32_t j = blockIdx.x >> 3;
-    split = j % S::NSPLIT;
-    part = (j / S::NSPLIT) * 8 + (blockIdx.x & 7);
-  }
-  if (part >= p.npart) return;
-  const uint32_t st_begin = (uint32_t)((uint64_t)part * p.nunits / p.npart) * SUB;
-  const uint32_t st_end = (uint32_t)((uint64_t)(part + 1) * p.nunits / p.npart) * SUB;
-  const int r0 = (int)split * S::RTS * 16;  // first stacked row of this workgroup
-  const int r1 = min(r0 + S::RTS * 16, 3 * NP);
-
-  // Pad entries (columns Np.. of u, rows r1-r0.. of W) feed only outputs that
-  // are never stored; keep them finite.
-  for (int x = tid; x < 2 * S::STAGE_DOUBLES; x += S::NTH) lds[x] = 0.0;
-  __syncthreads();
-
-  // this thread's column within a step and its first row
-  const int cc = tid / S::TPC;
-  const int rr = tid % S::TPC;
-  // the workgroup's rows start in direction a_lo and span at most NDIR directions;
-  // rG holds the geometric factors of those (rows 3 a .. 3 a + 2 of the element's 9)
-  const int a_lo = S::NSPLIT > 1 ? r0 / NP : 0;
-  double ru[S::NXU], rg0[S::NXU], rg1[S::NXU], rg2[S::NXU], rG[3 * S::NDIR];
-  auto load = [&](uint32_t st) __attribute__((always_inline)) {
-    const uint32_t col = st * CH + cc;
-    const bool v = col < p.ncols;
-    const int64_t base = (int64_t)col * NP;
-#pragma unroll
-    for (int q = 0; q < S::NXU; ++q) {
-      const int i = rr + S::TPC * q;
-      const bool ok = v && i < NP;
-      ru[q] = ok ? p.u[base + i] : 0.0;
-      rg0[q] = ok ? p.gout[base + i] : 0.0;
-      rg1[q] = ok ? p.gout[p.plane + base + i] : 0.0;
-      rg2[q] = ok ? p.gout[2 * p.plane + base + i] : 0.0;
-    }
-    const int64_t gb = (int64_t)(v ? col / p.F : 0u) * 9;
-#pragma unroll
-    for (int d = 0; d < S::NDIR; ++d)
-#pragma unroll
-      for (int b = 0; b < 3; ++b) rG[3 * d + b] = v ? p.G[gb + 3 * min(a_lo + d, 2) + b] : 0.0;
-  };
-
-  // write the registers' step into staging buffer b
-  auto stage = [&](int b) __attribute__((always_inline)) {
-    double* ul = lds + b * S::STAGE_DOUBLES;
-    double* wl = ul + CH * S::LDU;
-#pragma unroll
-    for (int q = 0; q < S::NXU; ++q) {
-      const int i = rr + S::TPC * q;
-      if (i < NP) {
-        ul[cc * S::LDU + i] = ru[q];
-#pragma unroll
-        for (int d = 0; d < S::NDIR; ++d) {
-          const int r = (a_lo + d) * NP + i;
-          if (r >= r0 && r < r1)
-            wl[cc * S::LDW + (r - r0)] = rG[3 * d] * rg0[q] + rG[3 * d + 1] * rg1[q] + rG[3 * d + 2] * rg2[q];
-        }
-      }
-    }
-  };
-
-  f64x4 acc[S::TPW];
-#pragma unroll
-  for (int t = 0; t < S::TPW; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-
-  // prologue: step st_begin staged in buffer 0, step st_begin + 1 in registers
-  if (st_begin < st_end) {
-    load(st_begin);
-    stage(0);
-    if (st_begin + 1 < st_end) load(st_begin + 1);
-  }
-  __syncthreads();
-  int cur = 0;
-  for (uint32_t st = st_begin; st < st_end; ++st) {
-    // the other buffer was last read by the products of the previous step,
-    // which every wave finished before the barrier that ended it
-    if (st + 1 < st_end) {
-      stage(cur ^ 1);
-      if (st + 2 < st_end) load(st + 2);
-    }
-    const double* ul = lds + cur * S::STAGE_DOUBLES;
-    const double* wl = ul + CH * S::LDU;
-#pragma unroll
-    for (int t = 0; t < S::TPW; ++t) {
-      const int slot = wave * S::TPW + t;
-      if (slot < S::SLOTS) {
-        const int T = slot / S::KSPLIT;
-        const int ks = slot % S::KSPLIT;
-        const int rt = T / S::NB;
-        const int jb = T % S::NB;
-        const double* wa = wl + rt * 16 + (lane & 15);
-        const double* ub = ul + jb * 16 + (lane & 15);
-#pragma unroll
-        for (int kk = ks; kk < CH / 4; kk += S::KSPLIT) {
-          const int c = 4 * kk + (lane >> 4);
-          acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(wa[c * S::LDW], ub[c * S::LDU], acc[t], 0, 0, 0);
-        }
-      }
-      // one slot's operands at a time: keeps the LDS reads from being hoisted
-      // into registers for every slot at once
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();  // the next step's staging is visible; this buffer is free
-    cur ^= 1;
-  }
-
-  // Add the k shares of each tile (fixed order) and store the partial sum.
-  double* w = p.work + (int64_t)part * 3 * NP * NP;
-  auto store_tile = [&](int T, const f64x4& v) __attribute__((always_inline)) {
-    const int rt = T / S::NB;
-    const int jb = T % S::NB;
-    const int j = jb * 16 + (lane & 15);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int r = r0 + rt * 16 + 4 * q + (lane >> 4);
-      if (r < r1 && j < NP) w[(int64_t)r * NP + j] = v[q];
-    }
-  };
-  if constexpr (S::KSPLIT == 1) {
-#pragma unroll
-    for (int t = 0; t < S::TPW; ++t) {
-      const int slot = wave * S::TPW + t;
-      if (slot < S::SLOTS) store_tile(slot, acc[t]);
-    }
-  } else {
-    __syncthreads();  // staging buffers are reused for the k shares
-#pragma unroll
-    for (int t = 0; t < S::TPW; ++t) {
-      const int slot = wave * S::TPW + t;
-      if (slot < S::SLOTS) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) lds[(slot * 4 + q) * WAVE + lane] = acc[t][q];
-      }
-    }
-    __syncthreads();
-    for (int T = wave; T < S::NTW; T += GD_WPB) {
-      f64x4 v = f64x4{0.0, 0.0, 0.0, 0.0};
-      for (int ks = 0; ks < S::KSPLIT; ++ks) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] += lds[((T * S::KSPLIT + ks) * 4 + q) * WAVE + lane];
-      }
-      store_tile(T, v);
-    }
-  }
-}
-
-// ------------------------------------------------------------------ order 5: producer and consumer waves
-//
-// At Np = 56 the workgroup's waves take two roles.  Consumer waves 0..3 (one
-// per SIMD) hold the output tiles in their accumulators and run the products
-// of each step from LDS (the tiling is described below).  Producer waves
-// 4..7 load u and gout two steps ahead (16-byte accesses of node pairs) and
-// G one step ahead (one factor per lane, handed to the column's 16-lane row
-// by a DPP broadcast), form W and stage both into the LDS buffer of the next
-// step.  One barrier per step.  Each output accumulates its k steps in column
-// order, so the partial sums depend on (K, F) only.
-struct GdSplit56 {
-  static constexpr int NP = 56;
-  static constexpr int WPB = 8;
-  static constexpr int NTH = WAVE * WPB;
-  static constexpr int NCONS = 4;                    // consumer waves (column blocks)
-  static constexpr int NPRODT = NTH - NCONS * WAVE;  // producer threads
-  static constexpr int NB = 4, RT = 11;
-  static constexpr int CH = 16;                      // columns per step
-  static constexpr int KST = CH / 4;                 // k steps per step
-  static constexpr int LDU = gd_ld(16 * NB);
-  static constexpr int LDW = gd_ld(16 * RT);
-  static constexpr int STAGE_DOUBLES = CH * (LDU + LDW);
-  static constexpr int TPC = NPRODT / CH;            // producer threads per column (one DPP row)
-  static constexpr int NPR = (NP / 2 + TPC - 1) / TPC;  // node pairs per producer thread and plane
-  static constexpr int NXU = 2 * NPR;                // values per producer thread and plane
-  static constexpr int DEPTH = 2;                    // steps the loads run ahead
-  static_assert(GD_UNIT % CH == 0, "staging step");
-  static_assert(2 * 2 * STAGE_DOUBLES * 8 <= 160 * 1024, "two workgroups per CU");
-  static_assert(TPC * NXU <= LDU && 3 * NP + TPC * NXU - NP <= LDW, "nodes past Np land in the pads");
-  static_assert(TPC == 16 && NP % 2 == 0 && LDU % 2 == 0 && LDW % 2 == 0, "16-byte pairs, rows of 16 lanes");
-};
-
-// The consumers' tiling of the [168 x 56] output (rows r = a Np + i, columns
-// j) without padding.  Two matrix instructions run at the same flop rate:
-// v_mfma_f64_16x16x4f64 (one 16 x 16 tile, lane i + 16k holds row i of A and
-// column i of B for k step k) and v_mfma_f64_4x4x4f64 (four 4 x 4 blocks b,
-// lane 16k + 4b + x holds row x of block b's A and column x of its B; the
-// result of row i, column j of block b is in lane 16i + 4b + j).  Four kinds
-// of products:
-//   F(rt, cb)  16 x 16 tile, rows 16rt.., columns 16cb..      (rt < 10, cb < 3)
-//   C(rt, cq)  16 x 4: block b = rows 16rt + 4b.., columns 4cq..  (cq = 12, 13)
-//   R(rq, cb)  4 x 16: block b = rows 4rq.., columns 16cb + 4b..  (rq = 40, 41)
-//   K          8 x 8: block b = rows 160 + 4(b >> 1).., columns 48 + 4(b & 1)..
-// A C product reads the same A register as F(rt, .) and an R product the same
-// B register as F(., cb), so the 168 x 56 outputs take 30 F + 20 C + 6 R + 1 K
-// products with no padding, where 16-wide tiles alone execute 1.20x the useful
-// products.  Consumer wave w < 3 takes F(0..8, w) and R(40, w) (592 matrix-core
-// cycles per k step, 64 per F product and 16 per small one); wave 3 takes the
-// C products, F(9, .), R(41, .) and K (576 cycles).
-//
-// Each product reads two operand slots (a slot is one row range of W or one
-// column range of u, of one lane layout).  A slot's value for k step kk is
-// read from LDS GD56_LEAD product cycles before its first use (at the start
-// of the step at the latest), so only the values in flight are live.
-struct Gd56Plan {
-  static constexpr int MAXOP = 28, MAXSLOT = 20, MAXRD = 4 * MAXSLOT, MAXPOS = 4 * MAXOP + 1;
-  int nop = 0, nslot = 0, nrd = 0;
-  int kind[MAXOP] = {};       // 0 F, 1 C, 2 R, 3 K
-  int p1[MAXOP] = {}, p2[MAXOP] = {};
-  int acc[MAXOP] = {};        // accumulator index within the kind's bank (F or small)
-  int sa[MAXOP] = {}, sb[MAXOP] = {};
-  int nfull = 0, nsmall = 0;
-  int stype[MAXSLOT] = {};    // lane layout: 0 A rows 16.., 1 B cols 16.., 2 A rows 4.., 3 B cols 4.., 4 A of K, 5 B of K
-  int soff[MAXSLOT] = {};     // first row or column of the slot
-  // reads in issue order: k step and slot; position = product index (over the
-  // step's KST k steps) before which the read is issued
-  int rd_kk[MAXRD] = {}, rd_slot[MAXRD] = {};
-  int rd_begin[MAXPOS + 1] = {};  // reads issued before product n: rd_begin[n] .. rd_begin[n + 1] - 1
-};
-
-constexpr int GD56_LEAD = 320;
-constexpr int gd56_cycles(int kind) { return kind == 0 ? 64 : 16; }
-
-constexpr int gd56_slot(Gd56Plan& P, int type, int off) {
-  for (int x = 0; x < P.nslot; ++x)
-    if (P.stype[x] == type && P.soff[x] == off) return x;
-  P.stype[P.nslot] = type;
-  P.soff[P.nslot] = off;
-  return P.nslot++;
-}
-
-constexpr void gd56_add(Gd56Plan& P, int kind, int p1, int p2) {
-  const int o = P.nop++;
-  P.kind[o] = kind;
-  P.p1[o] = p1;
-  P.p2[o] = p2;
-  P.acc[o] = kind == 0 ? P.nfull++ : P.nsmall++;
-  switch (kind) {
-    case 0: P.sa[o] = gd56_slot(P, 0, 16 * p1); P.sb[o] = gd56_slot(P, 1, 16 * p2); break;
-    case 1: P.sa[o] = gd56_slot(P, 0, 16 * p1); P.sb[o] = gd56_slot(P, 3, 4 * p2); break;
-    case 2: P.sa[o] = gd56_slot(P, 2, 4 * p1); P.sb[o] = gd56_slot(P, 1, 16 * p2); break;
-    default: P.sa[o] = gd56_slot(P, 4, 160); P.sb[o] = gd56_slot(P, 5, 48); break;
-  }
-}
-
-constexpr Gd56Plan gd56_plan(int wv, int kst) {
-  Gd56Plan P;
-  if (wv < 3) {
-    for (int rt = 0; rt < 9; ++rt) gd56_add(P, 0, rt, wv);
-    gd56_add(P, 2, 40, wv);
-  } else {
-    for (int rt = 0; rt < 10; ++rt) {
-      gd56_add(P, 1, rt, 12);
-      gd56_add(P, 1, rt, 13);
-      if (rt >= 7) {
-        gd56_add(P, 0, 9, rt - 7);
-        gd56_add(P, 2, 41, rt - 7);
-      }
-    }
-    gd56_add(P, 3, 0, 0);
-  }
-  // read schedule over the step's kst k steps (products n = kk * nop + o)
-  const int N = kst * P.nop;
-  int pos[Gd56Plan::MAXRD] = {}, first[Gd56Plan::MAXRD] = {};
-  for (int kk = 0; kk < kst; ++kk) {
-    for (int x = 0; x < P.nslot; ++x) {
-      int u = -1;
-      for (int o = 0; o < P.nop && u < 0; ++o)
-        if (P.sa[o] == x || P.sb[o] == x) u = kk * P.nop + o;
-      int n = u, cyc = 0;
-      while (n > 0 && cyc < GD56_LEAD) {
-        --n;
-        cyc += gd56_cycles(P.kind[n % P.nop]);
-      }
-      pos[P.nrd] = n;
-      first[P.nrd] = u;
-      P.rd_kk[P.nrd] = kk;
-      P.rd_slot[P.nrd] = x;
-      ++P.nrd;
-    }
-  }
-  // order by position, then by first use (insertion sort)
-  for (int i = 1; i < P.nrd; ++i)
-    for (int j = i; j > 0 && (pos[j - 1] > pos[j] || (pos[j - 1] == pos[j] && first[j - 1] > first[j])); --j) {
-      int t = pos[j]; pos[j] = pos[j - 1]; pos[j - 1] = t;
-      t = first[j]; first[j] = first[j - 1]; first[j - 1] = t;
-      t = P.rd_kk[j]; P.rd_kk[j] = P.rd_kk[j - 1]; P.rd_kk[j - 1] = t;
-      t = P.rd_slot[j]; P.rd_slot[j] = P.rd_slot[j - 1]; P.rd_slot[j - 1] = t;
-    }
-  int m = 0;
-  for (int n = 0; n <= N; ++n) {
-    P.rd_begin[n] = m;
-    while (m < P.nrd && pos[m] == n) ++m;
-  }
-  P.rd_begin[N + 1] = m;
-  return P;
-}
-
-template <int WV>
-struct Gd56Wave {
-  static constexpr Gd56Plan P = gd56_plan(WV, GdSplit56::KST);
-  static_assert(P.nop <= Gd56Plan::MAXOP && P.nslot <= Gd56Plan::MAXSLOT, "plan size");
-  static_assert(P.nrd == GdSplit56::KST * P.nslot, "every slot read once per k step");
-};
-
 template <int I, int N, typename Fn>
-__device__ __forceinline__ void gd_static_for(Fn& fn) {
+__device__ __forceinline__ void gd_static_for(Fn&& fn) {
   if constexpr (I < N) {
     fn(std::integral_constant<int, I>{});
     gd_static_for<I + 1, N>(fn);
   }
 }
 
-// One consumer wave: its products for every step of the range, then its part
-// of the partial sum.
-template <int WV>
-__device__ __forceinline__ void gd56_consume(const double* __restrict__ lds, uint32_t nsteps, double* __restrict__ w,
-                                             int lane) {
-  using S = GdSplit56;
-  using PW = Gd56Wave<WV>;
-  constexpr int NP = S::NP;
-  constexpr int NOP = PW::P.nop, NSLOT = PW::P.nslot, NFULL = PW::P.nfull, NSMALL = PW::P.nsmall;
-  constexpr int N = S::KST * NOP;
-  const int kq = lane >> 4;
-  // per-lane word offset of each slot layout within a staging buffer (k step 0)
-  const int lane_off[6] = {S::CH * S::LDU + kq * S::LDW + (lane & 15),
-                           kq * S::LDU + (lane & 15),
-                           S::CH * S::LDU + kq * S::LDW + (lane & 3),
-                           kq * S::LDU + (lane & 3),
-                           S::CH * S::LDU + kq * S::LDW + 4 * ((lane >> 3) & 1) + (lane & 3),
-                           kq * S::LDU + 4 * ((lane >> 2) & 1) + (lane & 3)};
-  f64x4 accf[NFULL > 0 ? NFULL : 1];
-  double accs[NSMALL > 0 ? NSMALL : 1];
+// A wave's share: row group rg_ (LAST: of the last kind), directions a0 .. a0 + ND - 1, over column
+// slice `slice` of the part.
+template <int NP, bool LAST, int ND>
+__device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t slice, int rg_, int a0, double* lds) {
+  using S = GdShape<NP>;
+  constexpr int NF = S::NF, NQ = S::NQ;
+  constexpr int NR = S::nt(LAST), XT = S::xt(LAST);
+  constexpr bool X = XT >= 0;
+  constexpr int NRQ = S::rq(LAST) ? NQ : 0;
+  const int T0 = S::NRG > 1 ? S::t0(rg_) : 0;  // first tile
+  const int XD = ND == 1 ? 0 : rg_;            // direction of the extra tile (past a0)
+  const bool xon = ND == 3 || rg_ == 0;        // (one direction: the first group takes it)
+  constexpr bool ONE = NP == 4;       // one quad, nothing else: 16 columns a k-step
+  constexpr int CPS = ONE ? 16 : 4;   // columns per k-step
+  constexpr int NG = NR + (X ? 1 : 0) + NRQ;  // gout registers per plane: tiles, extra tile, quads
+  constexpr int NU = NF + NQ;                 // u registers: tiles, quads
+  constexpr int DEPTH = 2;            // gout register sets
+  constexpr int UD = NP >= 84 ? 1 : DEPTH;  // u register sets
+  const int lane = threadIdx.x & 63;
+  const int n = lane & 15, g = lane >> 4;
+
+  // this wave's columns, from c_lo: its slice of the part's range, which comes
+  // in units of a whole number of DEPTH k-steps per slice
+  constexpr uint32_t UNIT = S::SLICES * DEPTH * CPS;
+  static_assert(GD_UNIT % UNIT == 0, "every part has a unit");
+  const uint32_t nunits = (p.ncols + UNIT - 1) / UNIT;
+  const uint32_t u_lo = (uint32_t)((uint64_t)part * nunits / p.npart);
+  const uint32_t u_hi = (uint32_t)((uint64_t)(part + 1) * nunits / p.npart);
+  // (wave-uniform for certain: the buffer descriptors are built from them)
+  const uint32_t per_wave = __builtin_amdgcn_readfirstlane((u_hi - u_lo) * (DEPTH * CPS));
+  const uint32_t c_lo = __builtin_amdgcn_readfirstlane(u_lo * UNIT) + slice * per_wave;
+  const uint32_t nsteps = per_wave / CPS;
+
+  // The lane's byte offsets within a k-step's columns.  A quad register holds
+  // node 16 NF + 4 q + (lane & 3) in lane group of 4 lanes b = (lane >> 2) & 3,
+  // with q = 0 for one quad; for two, q = b & 1 in the first register and the
+  // other quad in the second.  Nodes past Np: past every range.
+  const int cl = ONE ? lane >> 2 : g;  // column within the k-step
+  constexpr uint32_t OUT = 0x40000000u;
+  uint32_t base_off = NP == 10 && n >= NP ? OUT : (uint32_t)(cl * NP + n) * 8u;  // tile t: + 128 t
+  uint32_t tile_off = base_off + 128u * (uint32_t)T0;
+  uint32_t qoff[2];
 #pragma unroll
-  for (int t = 0; t < NFULL; ++t) accf[t] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int t = 0; t < NSMALL; ++t) accs[t] = 0.0;
-  __syncthreads();
-  for (uint32_t r = 0; r < nsteps; ++r) {
-    const double* buf = lds + (int)(r & 1u) * S::STAGE_DOUBLES;
-    double v[S::KST][NSLOT];
-    auto product = [&](auto nc) __attribute__((always_inline)) {
-      constexpr int n = decltype(nc)::value;
-      // the reads placed before product n (all of them, for n == N)
-      constexpr int rb = PW::P.rd_begin[n], re = PW::P.rd_begin[n + 1];
-      auto read = [&](auto ic) __attribute__((always_inline)) {
-        constexpr int m = rb + decltype(ic)::value;
-        constexpr int kk = PW::P.rd_kk[m], x = PW::P.rd_slot[m];
-        constexpr int ty = PW::P.stype[x];
-        constexpr int ld = (ty == 0 || ty == 2 || ty == 4) ? S::LDW : S::LDU;
-        v[kk][x] = buf[lane_off[ty] + 4 * kk * ld + PW::P.soff[x]];
-      };
-      gd_static_for<0, re - rb>(read);
-      if constexpr (re > rb) __builtin_amdgcn_sched_group_barrier(0x100, re - rb, 0);
-      if constexpr (n < N) {
-        constexpr int kk = n / NOP, o = n % NOP;
-        constexpr int a = PW::P.sa[o], b = PW::P.sb[o], t = PW::P.acc[o];
-        if constexpr (PW::P.kind[o] == 0)
-          accf[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[kk][a], v[kk][b], accf[t], 0, 0, 0);
-        else
-          accs[t] = __builtin_amdgcn_mfma_f64_4x4x4f64(v[kk][a], v[kk][b], accs[t], 0, 0, 0);
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      }
-    };
-    gd_static_for<0, N + 1>(product);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();  // the producers have staged step r + 1; buffer r % 2 is free
+  for (int q = 0; q < 2; ++q) {
+    const int node = 16 * NF + (NQ == 2 ? ((n & 7) ^ (4 * q)) : (n & 3));
+    qoff[q] = node < NP ? (uint32_t)(cl * NP + node) * 8u : OUT;
   }
-  // partial sums: output row and column of each product's results
+
+  // element (relative to the slice's first) and position in it of the lane's
+  // column, advanced by CPS columns a step
+  const uint32_t F = p.F;
+  const uint32_t k_lo = c_lo / F;
+  uint32_t ke, kr;
+  {
+    const uint32_t c = c_lo - k_lo * F + (uint32_t)cl;
+    ke = c / F;
+    kr = c - ke * F;
+  }
+  const uint32_t dk = CPS / F, dr = CPS % F;
+  const uint32_t n_el = c_lo < p.ncols ? (min(c_lo + per_wave, p.ncols) - 1u) / F - k_lo + 1u : 0u;
+  const __amdgpu_buffer_rsrc_t rG = buffer_range(p.G + (int64_t)k_lo * 9, n_el * 72u);
+  const uint32_t gf = ND == 3 ? (uint32_t)min(n, 8) : (uint32_t)(3 * a0 + min(n, 2));  // lane n of a row takes factor 3 a0 + n
+
+  double raw[DEPTH][3][NG], ru[UD][NU], rg[DEPTH][ONE ? 9 : 1];
+  auto columns = [&](uint32_t s, int64_t& base, uint32_t& nb) __attribute__((always_inline)) {
+    const uint32_t c0 = c_lo + s * CPS;
+    const uint32_t ncl = s < nsteps ? cols_left(p.ncols, c0, CPS) : 0u;
+    base = (int64_t)(ncl ? c0 : 0u) * NP;
+    nb = ncl * NP * 8u;
+  };
+  auto range_u = [&](uint32_t s) __attribute__((always_inline)) {
+    int64_t base;
+    uint32_t nb;
+    columns(s, base, nb);
+    return buffer_range(p.u + base, nb);
+  };
+  auto load_u = [&](const __amdgpu_buffer_rsrc_t& bu, int d, int x) __attribute__((always_inline)) {
+    ru[d][x] = buffer_load_f64(bu, x < NF ? base_off + 128u * x : qoff[x < NF ? 0 : x - NF]);
+  };
+  auto load_g = [&](uint32_t s, auto Dc) __attribute__((always_inline)) {
+    constexpr int d = decltype(Dc)::value;
+    int64_t base;
+    uint32_t nb;
+    columns(s, base, nb);
 #pragma unroll
-  for (int o = 0; o < NOP; ++o) {
-    const int kind = PW::P.kind[o], p1 = PW::P.p1[o], p2 = PW::P.p2[o], t = PW::P.acc[o];
-    const int b = (lane >> 2) & 3;
-    if (kind == 0) {
+    for (int b = 0; b < 3; ++b) {
+      const __amdgpu_buffer_rsrc_t bg = buffer_range(p.gout + b * p.plane + base, nb);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) w[(int64_t)(16 * p1 + 4 * q + kq) * NP + 16 * p2 + (lane & 15)] = accf[t][q];
-    } else if (kind == 1) {
-      w[(int64_t)(16 * p1 + 4 * b + kq) * NP + 4 * p2 + (lane & 3)] = accs[t];
-    } else if (kind == 2) {
-      w[(int64_t)(4 * p1 + kq) * NP + 16 * p2 + (lane & 15)] = accs[t];
+      for (int t = 0; t < NR; ++t) raw[d][b][t] = buffer_load_f64(bg, tile_off + 128u * t);
+      if constexpr (X) raw[d][b][NR] = buffer_load_f64(bg, base_off + 128u * XT);
+#pragma unroll
+      for (int q = 0; q < NRQ; ++q) raw[d][b][NG - NRQ + q] = buffer_load_f64(bg, qoff[q]);
+    }
+    if constexpr (ONE) {  // a row of 16 lanes holds 4 columns: no broadcast
+#pragma unroll
+      for (int c = 0; c < 9; ++c) rg[d][c] = buffer_load_f64(rG, (ke * 9u + (uint32_t)c) * 8u);
     } else {
-      w[(int64_t)(160 + 4 * (b >> 1) + kq) * NP + 48 + 4 * (b & 1) + (lane & 3)] = accs[t];
+      rg[d][0] = buffer_load_f64(rG, (ke * 9u + gf) * 8u);
+    }
+    ke += dk;
+    kr += dr;
+    if (kr >= F) {
+      kr -= F;
+      ++ke;
+    }
+  };
+
+  // accumulators: tiles; C (row tile x quad columns), R (quad rows x column
+  // tile), K (quad x quad); the extra tile's
+  f64x4 accF[ND][NR > 0 ? NR : 1][NF > 0 ? NF : 1], accX[NF > 0 ? NF : 1];
+  double accC[ND][NR > 0 ? NR : 1][NQ > 0 ? NQ : 1], accXC[NQ > 0 ? NQ : 1];
+  double accR[ND][NRQ > 0 ? NRQ : 1][NF > 0 ? NF : 1], accK[ND][NQ > 0 ? NQ : 1];
+#pragma unroll
+  for (int a = 0; a < ND; ++a) {
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+#pragma unroll
+      for (int j = 0; j < NF; ++j) accF[a][t][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < NQ; ++q) accC[a][t][q] = 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < NRQ; ++q) {
+#pragma unroll
+      for (int j = 0; j < NF; ++j) accR[a][q][j] = 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) accK[a][q] = 0.0;
+  }
+#pragma unroll
+  for (int j = 0; j < NF; ++j) accX[j] = f64x4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) accXC[q] = 0.0;
+
+  auto step = [&](uint32_t s, auto Dc) __attribute__((always_inline)) {
+    constexpr int d = decltype(Dc)::value;
+    // (the tiles' 128 t then fold into the loads, not into registers of their own)
+    asm volatile("" : "+v"(base_off), "+v"(tile_off));
+    // W of the k-step, then gout of step s + DEPTH into its registers
+    double W[ND][NG], WX = 0.0, x0 = 0.0, x1 = 0.0, x2 = 0.0;
+    gd_static_for<0, ND>([&](auto Ac) __attribute__((always_inline)) {
+      constexpr int a = decltype(Ac)::value;
+      double g0, g1, g2;
+      if constexpr (ONE) {
+        g0 = rg[d][3 * a];
+        g1 = rg[d][3 * a + 1];
+        g2 = rg[d][3 * a + 2];
+      } else {
+        g0 = row_bcast_f64<3 * a>(rg[d][0]);
+        g1 = row_bcast_f64<3 * a + 1>(rg[d][0]);
+        g2 = row_bcast_f64<3 * a + 2>(rg[d][0]);
+      }
+#pragma unroll
+      for (int t = 0; t < NG; ++t) {
+        if (X && t == NR) continue;
+        W[a][t] = g0 * raw[d][0][t] + g1 * raw[d][1][t] + g2 * raw[d][2][t];
+      }
+      if constexpr (X) {
+        if (a == 0 || XD == a) {  // (uniform)
+          x0 = g0;
+          x1 = g1;
+          x2 = g2;
+        }
+      }
+      if constexpr (NP >= 56) __builtin_amdgcn_sched_barrier(0);  // (else all 9 broadcasts are held at once)
+    });
+    if constexpr (X) WX = x0 * raw[d][0][NR] + x1 * raw[d][1][NR] + x2 * raw[d][2][NR];
+    load_g(s + DEPTH, Dc);
+    __builtin_amdgcn_sched_barrier(0);
+    // u feeds the products directly: one register at a time, reloaded after its
+    // products.  (Raised priority: products before another wave's vector work, -1 %.)
+    __builtin_amdgcn_s_setprio(1);
+    constexpr int ud = d % UD;
+    const __amdgpu_buffer_rsrc_t bu = range_u(s + UD);
+#pragma unroll
+    for (int j = 0; j < NF; ++j) {
+      const double U = ru[ud][j];
+#pragma unroll
+      for (int a = 0; a < ND; ++a) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+          accF[a][t][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(W[a][t], U, accF[a][t][j], 0, 0, 0);
+#pragma unroll
+        for (int q = 0; q < NRQ; ++q)
+          accR[a][q][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(W[a][NG - NRQ + q], U, accR[a][q][j], 0, 0, 0);
+      }
+      if constexpr (X) {
+        if (xon) accX[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(WX, U, accX[j], 0, 0, 0);
+      }
+      load_u(bu, ud, j);
+      if constexpr (UD == 1) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      const double U = ru[ud][NF + q];
+#pragma unroll
+      for (int a = 0; a < ND; ++a) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t)
+          accC[a][t][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(W[a][t], U, accC[a][t][q], 0, 0, 0);
+        // the first quad register of W against every one of u covers every pair of quads
+        if constexpr (NRQ > 0)
+          accK[a][q] = __builtin_amdgcn_mfma_f64_4x4x4f64(W[a][NG - NRQ], U, accK[a][q], 0, 0, 0);
+      }
+      if constexpr (X) {
+        if (xon) accXC[q] = __builtin_amdgcn_mfma_f64_4x4x4f64(WX, U, accXC[q], 0, 0, 0);
+      }
+      load_u(bu, ud, NF + q);
+    }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  load_g(0, I0{});
+  load_g(1, I1{});
+#pragma unroll
+  for (int d = 0; d < UD; ++d) {
+    const __amdgpu_buffer_rsrc_t bu = range_u((uint32_t)d);
+#pragma unroll
+    for (int x = 0; x < NU; ++x) load_u(bu, d, x);
+  }
+  for (uint32_t s = 0; s < nsteps; s += DEPTH) {
+    step(s, I0{});
+    step(s + 1, I1{});
+    // The groups carry different loads; left alone they drift apart until the
+    // columns one has read have left the caches before the other needs them
+    // (order 5, K = 2^19: 702 us without, 662 at every 4 steps, 652 at 32).
+    if constexpr (S::NRG > 1) {
+      if (s % 32 == 30) __syncthreads();
     }
   }
-}
 
-__global__ __launch_bounds__(GdSplit56::NTH) __attribute__((amdgpu_waves_per_eu(4, 8)))
-void gd_split56_kernel(GdArgs p) {
-  using S = GdSplit56;
-  constexpr int NP = S::NP;
-  constexpr int CH = S::CH;
-  constexpr int SUB = GD_UNIT / CH;
-  __shared__ __attribute__((aligned(16))) double lds[2 * S::STAGE_DOUBLES];
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const uint32_t wave = __builtin_amdgcn_readfirstlane((uint32_t)tid >> 6);
-  const uint32_t part = blockIdx.x;
-  if (part >= p.npart) return;
-  const uint32_t st_begin = (uint32_t)((uint64_t)part * p.nunits / p.npart) * SUB;
-  const uint32_t st_end = (uint32_t)((uint64_t)(part + 1) * p.nunits / p.npart) * SUB;
-  const uint32_t nsteps = st_end - st_begin;
-
-
-  const bool consumer = wave < S::NCONS;
-  // ---- producer state: u and gout DEPTH steps ahead (register set r % DEPTH),
-  // the geometric factors one step ahead (one set).  Loads go through buffer
-  // ranges of the column's valid words (past them: zeros, no access), so no
-  // branch surrounds a load and the waits count exactly.
-  const int pt = tid - S::NCONS * WAVE;  // producer thread (valid when !consumer)
-  const int cc = consumer ? 0 : pt / S::TPC;
-  const int rr = consumer ? 0 : pt % S::TPC;
-  double ru[S::DEPTH][S::NXU], rg0[S::DEPTH][S::NXU], rg1[S::DEPTH][S::NXU], rg2[S::DEPTH][S::NXU];
-  double rG[9];
-  // The buffer ranges are the step's (wave-uniform base and size: one
-  // descriptor per wave); a lane's node past Np reads a word of the next
-  // column, which is never staged.
-  auto load_ug = [&](uint32_t r, int d) __attribute__((always_inline)) {
-    const uint32_t c0 = (st_begin + r) * CH;
-    const uint32_t ncl = r < nsteps && c0 < p.ncols ? min((uint32_t)CH, p.ncols - c0) : 0u;
-    const int64_t base = (int64_t)(ncl ? c0 : 0u) * NP;
-    const uint32_t nb = ncl * NP * 8u;
-    const __amdgpu_buffer_rsrc_t bu = buffer_range(p.u + base, nb);
-    const __amdgpu_buffer_rsrc_t b0 = buffer_range(p.gout + base, nb);
-    const __amdgpu_buffer_rsrc_t b1 = buffer_range(p.gout + p.plane + base, nb);
-    const __amdgpu_buffer_rsrc_t b2 = buffer_range(p.gout + 2 * p.plane + base, nb);
-    // nodes 2 (rr + 16 h) and the next one, as one 16-byte access per plane
+  if constexpr (ONE) {  // the four blocks hold four sets of columns: add them first
 #pragma unroll
-    for (int h = 0; h < S::NPR; ++h) {
-      const uint32_t off = (uint32_t)(cc * NP + 2 * (rr + S::TPC * h)) * 8u;
-      const WordVec<double, 2> x = buffer_load_vec<double, 2>(bu, off);
-      const WordVec<double, 2> y0 = buffer_load_vec<double, 2>(b0, off);
-      const WordVec<double, 2> y1 = buffer_load_vec<double, 2>(b1, off);
-      const WordVec<double, 2> y2 = buffer_load_vec<double, 2>(b2, off);
+    for (int a = 0; a < ND; ++a) {
+      accK[a][0] += __shfl_xor(accK[a][0], 4);
+      accK[a][0] += __shfl_xor(accK[a][0], 8);
+    }
+  }
+  // fn(accumulator, index, lane's byte offset, common byte offset) for every
+  // accumulator: rows and columns of its output; a lane without one has an
+  // offset past the partial sum
+  const int l = opaque(lane);
+  const int n1 = l & 15, g1 = l >> 4, b4 = (l >> 2) & 3, x4 = l & 3;
+  auto each = [&](auto&& fn) __attribute__((always_inline)) {
+    int x = 0;
+    uint32_t ot[4], oc[2], orr[2], ok[2];
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        ru[d][2 * h + e] = x.v[e];
-        rg0[d][2 * h + e] = y0.v[e];
-        rg1[d][2 * h + e] = y1.v[e];
-        rg2[d][2 * h + e] = y2.v[e];
+    for (int q = 0; q < 4; ++q)
+      ot[q] = NP != 10 || (4 * q + g1 < NP && n1 < NP) ? (uint32_t)(g1 * NP + n1) * 8u : OUT;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int nq = (NQ == 2 ? 4 * ((b4 & 1) ^ q) : 0);  // the quad's first node, past the tiles
+      const int r0 = (NQ == 2 ? 4 * (b4 & 1) : 0) + g1;
+      oc[q] = 16 * NF + nq + x4 < NP ? (uint32_t)((4 * b4 + g1) * NP + nq + x4) * 8u : OUT;
+      orr[q] = 16 * NF + nq + g1 < NP ? (uint32_t)((nq + g1) * NP + 4 * b4 + x4) * 8u : OUT;
+      ok[q] = 16 * NF + r0 < NP && 16 * NF + nq + x4 < NP && b4 < NQ ? (uint32_t)(r0 * NP + nq + x4) * 8u : OUT;
+    }
+    auto tile = [&](uint32_t row, const f64x4& v, int j) __attribute__((always_inline)) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) fn(v[q], x++, ot[q], ((row + 4 * q) * NP + 16 * j) * 8u);
+    };
+#pragma unroll
+    for (int a = 0; a < ND; ++a) {
+      const uint32_t rt = (uint32_t)((a0 + a) * NP + 16 * T0), rq = (uint32_t)((a0 + a) * NP + 16 * NF);
+#pragma unroll
+      for (int t = 0; t < NR; ++t) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) tile(rt + 16 * t, accF[a][t][j], j);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) fn(accC[a][t][q], x++, oc[q], ((rt + 16 * t) * NP + 16 * NF) * 8u);
+      }
+#pragma unroll
+      for (int q = 0; q < NRQ; ++q) {
+#pragma unroll
+        for (int j = 0; j < NF; ++j) fn(accR[a][q][j], x++, orr[q], (rq * NP + 16 * j) * 8u);
+      }
+      if constexpr (NRQ > 0) {
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) fn(accK[a][q], x++, ok[q], (rq * NP + 16 * NF) * 8u);
       }
     }
-  };
-  // The 9 geometric factors of a column's element: lane rr of the column's
-  // 16-lane row loads factor rr, and a row broadcast (DPP) hands each factor
-  // to the whole row, instead of 16 lanes loading the same 72 bytes.
-  double gv = 0.0;
-  auto load_g = [&](uint32_t r) __attribute__((always_inline)) {
-    const uint32_t c0 = (st_begin + r) * CH;
-    const uint32_t ncl = r < nsteps && c0 < p.ncols ? min((uint32_t)CH, p.ncols - c0) : 0u;
-    const uint32_t k0 = ncl ? c0 / p.F : 0u;
-    const uint32_t nk = ncl ? (c0 + ncl - 1) / p.F - k0 + 1 : 0u;
-    const __amdgpu_buffer_rsrc_t bg = buffer_range(p.G + (int64_t)k0 * 9, nk * 72u);
-    const uint32_t ke = (c0 + (uint32_t)cc) / p.F - k0;  // this lane's element within the step
-    gv = buffer_load_f64(bg, (ke * 9u + (uint32_t)min(rr, 8)) * 8u);
-  };
-  auto bcast_g = [&]() __attribute__((always_inline)) {
-    rG[0] = row_bcast_f64<0>(gv);
-    rG[1] = row_bcast_f64<1>(gv);
-    rG[2] = row_bcast_f64<2>(gv);
-    rG[3] = row_bcast_f64<3>(gv);
-    rG[4] = row_bcast_f64<4>(gv);
-    rG[5] = row_bcast_f64<5>(gv);
-    rG[6] = row_bcast_f64<6>(gv);
-    rG[7] = row_bcast_f64<7>(gv);
-    rG[8] = row_bcast_f64<8>(gv);
-  };
-  auto stage = [&](int d, int b) __attribute__((always_inline)) {
-    double* ul = lds + b * S::STAGE_DOUBLES;
-    double* wl = ul + CH * S::LDU;
-    bcast_g();
-    // A node past Np (the last pair of some threads) is written to the pads
-    // (u columns Np.., W rows 3 Np..), which no product reads: the writes need
-    // no branch, so the waits for the loads stay exact.
+    if constexpr (X) {
+      if (!xon) return;
+      const uint32_t rx = (uint32_t)((a0 + XD) * NP + 16 * XT);
 #pragma unroll
-    for (int h = 0; h < S::NPR; ++h) {
-      const int i = 2 * (rr + S::TPC * h);
-      const bool in = i < NP;
-      *reinterpret_cast<f64x2*>(ul + cc * S::LDU + i) = f64x2{ru[d][2 * h], ru[d][2 * h + 1]};
+      for (int j = 0; j < NF; ++j) tile(rx, accX[j], j);
 #pragma unroll
-      for (int a = 0; a < 3; ++a) {
-        f64x2 wv;
-#pragma unroll
-        for (int e = 0; e < 2; ++e)
-          wv[e] = rG[3 * a] * rg0[d][2 * h + e] + rG[3 * a + 1] * rg1[d][2 * h + e] + rG[3 * a + 2] * rg2[d][2 * h + e];
-        *reinterpret_cast<f64x2*>(wl + cc * S::LDW + (in ? a * NP + i : 3 * NP + i - NP)) = wv;
-      }
+      for (int q = 0; q < NQ; ++q) fn(accXC[q], x++, oc[q], (rx * NP + 16 * NF) * 8u);
     }
   };
-  // Each role runs its own loop (so that the consumers' accumulators and the
-  // producers' register sets are never live together), with the same barriers:
-  // one after the prologue, one per step.  Step r sits in producer register set
-  // r % DEPTH and staging buffer r % 2 (DEPTH = 2: both alternate with r).
-  if (consumer) {
-    double* w = p.work + (int64_t)part * 3 * NP * NP;
-    switch (wave) {
-      case 0: gd56_consume<0>(lds, nsteps, w, lane); break;
-      case 1: gd56_consume<1>(lds, nsteps, w, lane); break;
-      case 2: gd56_consume<2>(lds, nsteps, w, lane); break;
-      default: gd56_consume<3>(lds, nsteps, w, lane); break;
-    }
+  // add the slices' accumulators in order: the first writes, the next add theirs, the last adds and stores
+  const __amdgpu_buffer_rsrc_t rw = buffer_range(p.work + (int64_t)part * 3 * NP * NP, 3u * NP * NP * 8u);
+  auto store = [&](double v, uint32_t off, uint32_t common) __attribute__((always_inline)) {
+    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rw, (int)off, (int)common, 0);
+  };
+  if constexpr (S::SLICES == 1) {
+    each([&](double v, int, uint32_t off, uint32_t common) __attribute__((always_inline)) { store(v, off, common); });
   } else {
-    static_assert(S::DEPTH == 2, "register sets alternate with the step");
-    // The producers' vector work (FP64 multiply-adds, loads) shares the SIMDs
-    // with the consumers' matrix products, and every step waits for it at the
-    // barrier: issue it first (measured: 4 % faster).
-    __builtin_amdgcn_s_setprio(3);
-    if (nsteps > 0) {
-      load_ug(0, 0);
-      load_ug(1, 1);
-      load_g(0);
-      stage(0, 0);
-      load_g(1);
-      load_ug(2, 0);
-    }
-    __syncthreads();
-    // iteration r stages step r + 1 (its G requested one iteration earlier, its u and
-    // gout two), then requests G of step r + 2 and u, gout of step r + 3
-    // (nsteps is a whole number of partition units, so even: the pair of
-    // iterations needs no guard, and the waits for the loads stay exact)
-    static_assert(SUB % 2 == 0, "steps come in pairs");
-    for (uint32_t r0 = 0; r0 < nsteps; r0 += 2) {
+    constexpr int PL = S::acc_pass(LAST, ND);
+    double* mine = lds + l;
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const uint32_t r = r0 + j;
-        stage(j ^ 1, j ^ 1);
-        load_g(r + 2);
-        load_ug(r + 3, j ^ 1);
+    for (int pass = 0; pass < S::passes(ND); ++pass) {
+      const int x0 = pass * PL;
+#pragma unroll 1
+      for (uint32_t v = 0; v < S::SLICES; ++v) {
+        if (slice == v) {
+          if (v == 0)
+            each([&](double a, int x, uint32_t, uint32_t) __attribute__((always_inline)) {
+              if (x / PL == pass) mine[(x - x0) * WAVE] = a;
+            });
+          else if (v + 1 < S::SLICES)
+            each([&](double a, int x, uint32_t, uint32_t) __attribute__((always_inline)) {
+              if (x / PL == pass) mine[(x - x0) * WAVE] += a;
+            });
+          else
+            each([&](double a, int x, uint32_t off, uint32_t common) __attribute__((always_inline)) {
+              if (x / PL == pass) store(mine[(x - x0) * WAVE] + a, off, common);
+            });
+        }
         __syncthreads();
       }
     }
   }
 }
 
-// gD[x] = sum over parts of work[part][x], x < n, in a fixed order.
-// Block: 64 consecutive x by GD_RED_PG part groups; part group g adds parts
-// g, g + GD_RED_PG, ... in ascending order, and the group sums are then added
-// in ascending g.  With npart = 0 it writes zeros.
-constexpr int GD_RED_PG = 16;
+// Forms: a workgroup per part (ND = 3, RS = 1); with few parts, RS = 2
+// workgroups of half the row groups each (grid.z), or those for each direction
+// (ND = 1, grid.y), so that the chain of products of a part is half or a sixth
+// as long (a sum of 2 parts, orders 5 / 6 / 7: 17 / 24 / 27 -> 8 / 12 / 11 us).
+template <int NP, int ND, int RS>
+constexpr int gd_threads() { return GdShape<NP>::NTH / RS; }
 
-__global__ __launch_bounds__(64 * GD_RED_PG) void gd_reduce_kernel(const double* __restrict__ work,
-                                                                  double* __restrict__ gD, uint32_t npart,
-                                                                  uint32_t n) {
-  __shared__ double part_sum[GD_RED_PG][64];
-  const int xi = threadIdx.x & 63;
-  const int g = threadIdx.x >> 6;
-  const uint32_t x = blockIdx.x * 64 + xi;
+template <int NP, int ND, int RS>
+__global__ __launch_bounds__((gd_threads<NP, ND, RS>())) __attribute__((amdgpu_waves_per_eu(ND == 1 ? 3 : GdShape<NP>::WPS, 8)))
+void gd_partial_kernel(GdArgs p) {
+  using S = GdShape<NP>;
+  __shared__ double lds[S::lds_doubles(ND, RS)];
+  const uint32_t w0 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t slice, rg;
+  if constexpr (S::NRG == 1) {
+    slice = w0;
+    rg = 0;
+  } else if constexpr (RS > 1) {  // half z has row groups z NRG / 2 on
+    constexpr uint32_t H = S::NRG / RS;
+    slice = w0 / H;
+    rg = w0 % H + blockIdx.z * H;
+  } else {  // waves w and w + 4 share a SIMD: Np = 56: of the two groups; Np = 84: of neighbouring ones
+    slice = S::NRG == 2 ? w0 & 3u : S::NRG == 4 ? w0 >> 2 : 0u;
+    rg = S::NRG == 2 ? w0 >> 2 : S::NRG == 4 ? (w0 + slice) & 3u : w0;
+  }
+  double* mine = lds + (S::SLICES > 1 ? rg % (S::NRG / RS) * S::lds_group(ND) : 0);
+  // (both kinds run the same number of workgroup barriers)
+  if (S::NRG > 1 && rg + 1 < S::NRG)
+    gd_role<NP, S::NRG == 1, ND>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);
+  else
+    gd_role<NP, true, ND>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);
+}
+
+// gD[x] = sum over parts of work[part][x], x < n, in a fixed order.
+// Block: 16 consecutive x (whole cache lines) by GD_RED_PG part groups; part
+// group g adds parts g, g + GD_RED_PG, ... in ascending order, and the group
+// sums are then added in two ordered levels.  With 16 part groups of 64 x, one
+// block of order 1 walked 64 parts in a chain (18 us; now 4).  With npart = 0
+// it writes zeros.
+constexpr int GD_RED_PG = 64;
+constexpr int GD_RED_X = 16;
+
+__global__ __launch_bounds__(GD_RED_X * GD_RED_PG) void gd_reduce_kernel(const double* __restrict__ work,
+                                                                        double* __restrict__ gD, uint32_t npart,
+                                                                        uint32_t n) {
+  __shared__ double part_sum[GD_RED_PG][GD_RED_X];
+  const int xi = threadIdx.x % GD_RED_X;
+  const int g = threadIdx.x / GD_RED_X;
+  const uint32_t x = blockIdx.x * GD_RED_X + xi;
   double s = 0.0;
   if (x < n) {
-    for (uint32_t pt = g; pt < npart; pt += GD_RED_PG) s += work[(int64_t)pt * n + x];
+    for (uint32_t pt = g; pt < npart; pt += 4 * GD_RED_PG) {  // four reads in flight
+      double v[4];
+#pragma unroll
+      for (uint32_t h = 0; h < 4; ++h) v[h] = work[(int64_t)min(pt + h * GD_RED_PG, npart - 1u) * n + x];
+#pragma unroll
+      for (uint32_t h = 0; h < 4; ++h) s += pt + h * GD_RED_PG < npart ? v[h] : 0.0;
+    }
   }
   part_sum[g][xi] = s;
+  __syncthreads();
+  if (g < 8) {
+    s = 0.0;
+#pragma unroll
+    for (int h = 0; h < 8; ++h) s += part_sum[8 * g + h][xi];
+  }
+  __syncthreads();
+  if (g < 8) part_sum[g][xi] = s;
   __syncthreads();
   if (g == 0 && x < n) {
     double t = 0.0;
 #pragma unroll
-    for (int h = 0; h < GD_RED_PG; ++h) t += part_sum[h][xi];
+    for (int h = 0; h < 8; ++h) t += part_sum[h][xi];
     gD[x] = t;
   }
 }

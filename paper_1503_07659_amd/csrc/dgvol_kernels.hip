@@ -17,6 +17,7 @@
 #include <cmath>
 #include <cstdint>
 #include <mutex>
+#include <type_traits>
 
 #include "dgvol.h"
 #include "dgvol_adjoint.hpp"
@@ -384,8 +385,10 @@ static dg_status launch_adj_u_f64(const double* D, const double* G, const double
   return hipGetLastError() == hipSuccess ? DG_OK : DG_ELAUNCH;
 }
 
-// Partial sums of the D cotangent: a pure function of the problem size, so
-// the result does not depend on the device.
+// Partial sums the workspace of the D cotangent holds, and those launched (at
+// most that many: fewer, longer column ranges where one partial sum is large,
+// which the workgroups that fit the chip at once then share evenly).  Pure
+// functions of the problem size, so the result does not depend on the device.
 static uint32_t gd_parts(int64_t K, int32_t Np, int32_t F) {
   const uint32_t nunits = ceil_div((uint64_t)K * (uint64_t)F, GD_UNIT);
   return std::min<uint32_t>(nunits, gd_maxpart(Np));
@@ -398,20 +401,38 @@ static dg_status launch_gd_f64(const double* G, const double* u, const double* g
                                uint32_t npart, int64_t K, int32_t F, hipStream_t stream) {
   using S = GdShape<NP>;
   const uint64_t ncols = (uint64_t)K * (uint64_t)F;
+  npart = std::min<uint32_t>(npart, S::MAXPART);
   if (npart > 0) {
-    const GdArgs p{G, u, gout, work, (uint32_t)ncols, (uint32_t)F, (int64_t)ncols * NP, ceil_div(ncols, GD_UNIT),
-                   npart};
-    if constexpr (NP == 56) {
-      hipLaunchKernelGGL(gd_split56_kernel, dim3(npart), dim3(GdSplit56::NTH), 0, stream, p);
+    const GdArgs p{G, u, gout, work, (uint32_t)ncols, (uint32_t)F, (int64_t)ncols * NP, npart};
+    auto launch = [&](auto Nd, auto Rs) {
+      constexpr int ND = decltype(Nd)::value, RS = decltype(Rs)::value;
+      hipLaunchKernelGGL((gd_partial_kernel<NP, ND, RS>), dim3(npart, 3 / ND, RS), dim3(gd_threads<NP, ND, RS>()), 0,
+                         stream, p);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I3 = std::integral_constant<int, 3>;
+    // the finest form whose workgroups all have a CU of their own (of 256; at
+    // Np = 35, of half a CU)
+    if constexpr (NP >= 56) {
+      if (npart <= 42)
+        launch(I1{}, I2{});
+      else if (npart <= 128)
+        launch(I3{}, I2{});
+      else
+        launch(I3{}, I1{});
+    } else if constexpr (NP == 35) {
+      if (npart <= 128)
+        launch(I1{}, I1{});
+      else
+        launch(I3{}, I1{});
     } else {
-      // with NSPLIT > 1 the grid is rounded up to whole groups of 8 ranges (one per XCD)
-      const uint32_t grid = S::NSPLIT == 1 ? npart : ceil_div(npart, 8) * 8 * S::NSPLIT;
-      hipLaunchKernelGGL(gd_partial_kernel<NP>, dim3(grid), dim3(S::NTH), 0, stream, p);
+      launch(I3{}, I1{});
     }
   }
   const uint32_t n = 3u * NP * NP;
-  hipLaunchKernelGGL(gd_reduce_kernel, dim3(ceil_div(n, 64)), dim3(64 * GD_RED_PG), 0, stream, work, gD, npart,
-                     n);
+  hipLaunchKernelGGL(gd_reduce_kernel, dim3(ceil_div(n, GD_RED_X)), dim3(GD_RED_X * GD_RED_PG), 0, stream, work, gD,
+                     npart, n);
   return hipGetLastError() == hipSuccess ? DG_OK : DG_ELAUNCH;
 }
 
