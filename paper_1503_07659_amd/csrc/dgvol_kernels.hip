@@ -401,7 +401,14 @@ static dg_status launch_gd_f64(const double* G, const double* u, const double* g
                                uint32_t npart, int64_t K, int32_t F, hipStream_t stream) {
   using S = GdShape<NP>;
   const uint64_t ncols = (uint64_t)K * (uint64_t)F;
-  npart = std::min<uint32_t>(npart, S::MAXPART);
+  // From Np = 56, rows over two workgroups while the parts alone leave CUs idle
+  // (fewer than MAXPART = 256), and then at most 128 parts: 256 workgroups.
+  // One workgroup a part from 129 parts up left 116 of 256 CUs idle at 140
+  // parts.  F = 3, unsplit -> split: order 5, 1e6 nodal values 24.0 -> 20.5 us,
+  // 1.8e6 26.5 -> 25.8; order 6, 1.4e6 37.8 -> 27.9, 2.5e6 41.5 -> 37.9; order 7,
+  // 2e6 66.3 -> 45.8, 3.6e6 76.5 -> 71.3.  At 256 parts the chip is full without.
+  const bool split_rows = NP >= 56 && npart < S::MAXPART;
+  npart = std::min<uint32_t>(npart, split_rows ? 128u : S::MAXPART);
   if (npart > 0) {
     const GdArgs p{G, u, gout, work, (uint32_t)ncols, (uint32_t)F, (int64_t)ncols * NP, npart};
     auto launch = [&](auto Nd, auto Rs) {
@@ -417,7 +424,7 @@ static dg_status launch_gd_f64(const double* G, const double* u, const double* g
     if constexpr (NP >= 56) {
       if (npart <= 42)
         launch(I1{}, I2{});
-      else if (npart <= 128)
+      else if (split_rows)
         launch(I3{}, I2{});
       else
         launch(I3{}, I1{});

@@ -1,6 +1,6 @@
 """GPU parity of the D cotangent around the sizes where the launch takes another form (a part's row
-groups and directions on workgroups of their own up to 42 parts, row groups up to 128 parts, whole
-parts beyond; a part is 128 columns there), where the columns end inside a k-step of 4 or a unit
+groups and directions on workgroups of their own up to 42 parts of 128 columns; from order 5, row
+groups up to 255, on at most 128 longer parts; whole parts beyond), where the columns end inside a k-step of 4 or a unit
 of 16 to 128, and with pointers aligned to 8 bytes only.  Bound: the suite's 1e-12 pair against
 the FP64 oracle's full reduction."""
 
@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
 
 PARTS = [42 * 128, 42 * 128 + 1, 128 * 128 - 3, 128 * 128 + 2]
 CASES = [(N, c, 1) for N in (4, 5, 6, 7) for c in PARTS]
+CASES += [(N, c, 1) for N in (5, 6, 7) for c in (255 * 128, 255 * 128 + 1)]
 CASES += [(N, k, F) for N in range(1, 8) for k, F in ((1, 1), (3, 1), (2, 2), (33, 1), (7, 19), (43, 3))]
 
 
