@@ -15,7 +15,9 @@
 //     k-steps of three tiles each).  Per 16
 //     columns the workgroup forms W from gout and G (each thread stages a fixed
 //     column, so it needs one element's geometric factors) into LDS, each wave
-//     runs its k-steps, and gu leaves through an LDS tile as contiguous runs.
+//     runs its k-steps.  At Np = 84 gu leaves through an LDS tile as contiguous
+//     runs, where the helpers' sums are added; at Np = 120 straight from the
+//     accumulators (AdjCrA::DIRECT).
 //   pass B (gG):  gG[k][3a+b] = sum_f sum_i gout_b[c][i] (D_a u)[c][i].
 //     Wave w < NCH keeps the A operands of output chunk w (3 tiles, as the
 //     forward chunk-register body; at Np = 84, 4 tiles in 4-wave workgroups),
@@ -74,6 +76,16 @@ struct AdjCrA {
   // at Np = 120 the last KL k-steps' operands wait in LDS, not registers
   static constexpr int KL = NP == 120 ? 12 : 0;
   static constexpr int KR = KA - KL;
+  // Without helper waves (Np = 120) the columns are the matrix rows of the
+  // product, so a lane group's sums are 16 consecutive nodes of a column and are
+  // stored as 128-byte runs, and with W double-buffered a tile takes one
+  // barrier, not two: F = 3, gu and gG of 2e7 nodal values 567 -> 558 us, of 2e6
+  // 90.6 -> 89.2 (gu is bound by its products, of which the pass has no fewer).
+  // At Np = 84 the same lost 1 % (450 -> 455): the owners must wait a tile for
+  // the helpers' sums, and its 672-byte columns cut the runs across lines; nor
+  // did 12 % fewer products there (the last 4 nodes as 4x4x4) change its time.
+  static constexpr bool DIRECT = !SPLIT;
+  static_assert(!DIRECT || NP % 4 == 0, "k-steps of whole nodes");
   static_assert(!SPLIT || 3 * KB <= KA, "a helper wave's operands fit the owner's array");
 };
 
@@ -84,8 +96,8 @@ __global__ __launch_bounds__(WAVE* ADJCR_WPB) void adjcr_gu_kernel(const double*
                                                                   double* __restrict__ gu, uint32_t ncols, uint32_t F,
                                                                   int64_t plane, uint32_t ntiles) {
   using S = AdjCrA<NP>;
-  __shared__ double ws[16 * S::LDW];  // W[c][a Np + i]
-  __shared__ double ostg[16 * NP];    // gu tile, column-major runs
+  __shared__ double ws[S::DIRECT ? 2 : 1][16 * S::LDW];  // W[c][a Np + i]
+  __shared__ double ostg[S::DIRECT ? 1 : 16 * NP];         // gu tile, column-major runs
   __shared__ double ostg2[S::SPLIT ? 16 * NP : 1];  // the helper waves' partial
   __shared__ double atl[S::KL ? ADJCR_WPB * S::KL * WAVE : 1];  // operand tail, per wave and lane
   const int tid = threadIdx.x;
@@ -136,31 +148,35 @@ __global__ __launch_bounds__(WAVE* ADJCR_WPB) void adjcr_gu_kernel(const double*
   };
   // W of the loaded tile into the stage; done at the end of an iteration, after
   // its stores, so the wait for the loads does not cover those stores
-  auto stage = [&]() __attribute__((always_inline)) {
+  auto stage = [&](uint32_t b) __attribute__((always_inline)) {
 #pragma unroll
     for (int x = 0; x < S::NX; ++x) {
       const int i = rr + S::TPC * x;
       if (i < NP) {
 #pragma unroll
         for (int a = 0; a < 3; ++a)
-          ws[cc * S::LDW + a * NP + i] = rG[3 * a] * r0[x] + rG[3 * a + 1] * r1[x] + rG[3 * a + 2] * r2[x];
+          ws[b][cc * S::LDW + a * NP + i] = rG[3 * a] * r0[x] + rG[3 * a + 1] * r1[x] + rG[3 * a + 2] * r2[x];
       }
     }
   };
   constexpr int NST = (16 * NP + S::NTH - 1) / S::NTH;  // gu words stored per thread
-  uint32_t t = blockIdx.x;
+  // DIRECT: the lane holds node 16 w + n of columns 4 q + g (nodes past Np: past
+  // every range)
+  const uint32_t st_off = 16 * w + n < NP ? (uint32_t)(g * NP + 16 * w + n) * 8u : 0x40000000u;
+  uint32_t t = blockIdx.x, b = 0;
   load(min(t, ntiles - 1));
-  stage();
-  for (; t < ntiles; t += gridDim.x) {
+  stage(0);
+  for (; t < ntiles; t += gridDim.x, b ^= S::DIRECT) {
     const uint32_t col0 = t * 16;
     const int cnt = (int)min(16u, ncols - col0) * NP;
+    const __amdgpu_buffer_rsrc_t ro = buffer_range(gu + (int64_t)col0 * NP, (uint32_t)cnt * 8u);
     __syncthreads();
     load(min(t + gridDim.x, ntiles - 1));
     if (mma) {
       f64x4 acc = f64x4{0.0, 0.0, 0.0, 0.0};
       auto bval = [&](int sp) __attribute__((always_inline)) {
         const int i = 4 * (sp / 3) + g;
-        const double v = ws[n * S::LDW + (sp % 3) * NP + min(i, NP - 1)];
+        const double v = ws[b][n * S::LDW + (sp % 3) * NP + min(i, NP - 1)];
         return i < NP ? v : 0.0;
       };
       double bcur = bval(0);
@@ -168,13 +184,20 @@ __global__ __launch_bounds__(WAVE* ADJCR_WPB) void adjcr_gu_kernel(const double*
       for (int sp = 0; sp < S::KA; ++sp) {
         const double bnxt = sp + 1 < S::KA ? bval(sp + 1) : 0.0;
         const double a = sp < S::KR ? areg[sp] : atl[(w * S::KL + sp - S::KR) * WAVE + lane];
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bcur, acc, 0, 0, 0);
+        if constexpr (S::DIRECT)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(bcur, a, acc, 0, 0, 0);
+        else
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a, bcur, acc, 0, 0, 0);
         bcur = bnxt;
       }
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int j = 16 * w + 4 * q + g;
-        if (j < NP) ostg[n * NP + j] = acc[q];
+        if constexpr (S::DIRECT) {
+          buffer_store_f64(ro, st_off + (uint32_t)(4 * q * NP) * 8u, acc[q]);
+        } else {
+          const int j = 16 * w + 4 * q + g;
+          if (j < NP) ostg[n * NP + j] = acc[q];
+        }
       }
     }
     if constexpr (S::SPLIT) {
@@ -184,7 +207,7 @@ __global__ __launch_bounds__(WAVE* ADJCR_WPB) void adjcr_gu_kernel(const double*
         for (int r = 0; r < 3; ++r) acc[r] = f64x4{0.0, 0.0, 0.0, 0.0};
         auto bval = [&](int sp) __attribute__((always_inline)) {
           const int i = 4 * (sp / 3) + g;
-          const double v = ws[n * S::LDW + (sp % 3) * NP + min(i, NP - 1)];
+          const double v = ws[0][n * S::LDW + (sp % 3) * NP + min(i, NP - 1)];
           return i < NP ? v : 0.0;
         };
         double bcur = bval(S::KA);
@@ -206,18 +229,16 @@ __global__ __launch_bounds__(WAVE* ADJCR_WPB) void adjcr_gu_kernel(const double*
         }
       }
     }
-    __syncthreads();
-    const __amdgpu_buffer_rsrc_t ro = buffer_range(gu + (int64_t)col0 * NP, (uint32_t)cnt * 8u);
+    if constexpr (!S::DIRECT) {
+      __syncthreads();
 #pragma unroll
-    for (int q = 0; q < NST; ++q) {
-      const int x = tid + S::NTH * q;
-      const int xc = min(x, 16 * NP - 1);
-      if constexpr (S::SPLIT)
+      for (int q = 0; q < NST; ++q) {
+        const int x = tid + S::NTH * q;
+        const int xc = min(x, 16 * NP - 1);
         buffer_store_f64(ro, (uint32_t)x * 8u, ostg[xc] + ostg2[xc]);
-      else
-        buffer_store_f64(ro, (uint32_t)x * 8u, ostg[xc]);
+      }
     }
-    stage();
+    stage(S::DIRECT ? b ^ 1 : 0);
   }
 }
 
