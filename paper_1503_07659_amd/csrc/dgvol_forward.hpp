@@ -73,8 +73,9 @@ __device__ __forceinline__ uint32_t staged_worker(uint32_t bid, uint32_t nblk, u
   return nrun >= nblk * WPB ? bid * WPB + wave : wave * nblk + bid;
 }
 
-// The A-operand table of a staged body.  The callers request their first tile
-// before it, so that the two latencies overlap (a fifth of a small launch).
+// The A-operand table of a staged body.  The buffer-range and multi-tile forms
+// request their first tile before it, so that the two latencies overlap (a fifth
+// of a small launch).
 template <int NP, int WPB>
 __device__ __forceinline__ void build_fwd_table(const double* __restrict__ D, double* afr) {
   using Sh = Shape<NP>;
@@ -110,7 +111,10 @@ __device__ __forceinline__ void fwd_f64_staged_single(const FwdArgs<double>& p, 
   const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double* stg = stg_all + wave * TILE;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = staged_worker<WPB>(bid, nblk, wave, p.ntiles);
+  // Tiles spread over the workgroups (see staged_worker) up to three quarters of
+  // a tile a wave: order 4, F = 3, 8e5 nodal values 10.9 -> 9.9 us; at 1e6 no
+  // faster than neighbouring tiles.
+  uint32_t t = p.ntiles * 4 <= stride * 3 ? wave * nblk + bid : bid * WPB + wave;
   double raw[NRAW];
   auto load_raw = [&](uint32_t tt) {
     const double* __restrict__ src = p.u + (int64_t)tt * TILE;
@@ -121,8 +125,12 @@ __device__ __forceinline__ void fwd_f64_staged_single(const FwdArgs<double>& p, 
       raw[q] = x < cnt ? src[x] : 0.0;
     }
   };
-  if (t < p.ntiles) load_raw(t);
+  // The first tile is requested after the table is built: before it, this form's
+  // loop came out slower (order 4, F = 3, 3e6 nodal values 28.5 -> 28.8 us, 2e7
+  // 138.9 -> 139.4; one tile a wave, 1e6: 12.2 -> 11.6; a switch between the two:
+  // 29.0, 140.2).
   build_fwd_table<NP, WPB>(p.D, afr);
+  if (t < p.ntiles) load_raw(t);
   for (; t < p.ntiles; t += stride) {
     const uint32_t col0 = t * 16;
     const int cnt = (int)min(16u, p.ncols - col0) * NP;
