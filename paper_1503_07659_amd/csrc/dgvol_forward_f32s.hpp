@@ -41,7 +41,10 @@ __host__ __device__ inline bool f32_pairs_ok(const FwdArgs<float>& p) {
 }
 
 // The split A-operand table of a staged body.  (Requesting the first tile before it, as
-// the FP64 bodies do, made the mixed batch 9 % slower: 234 -> 254 us.)
+// the FP64 bodies do, made the mixed batch 9 % slower: 234 -> 254 us.  Few tiles dealt to
+// the workgroups first, as there: 3e5 nodal values, F = 3, order 4 9.3 -> 8.7 us, order 5
+// 9.6 -> 9.9, but the loops at 2e7 came out slower, order 1 90.6 -> 91.2, order 3 61.1 ->
+// 61.5, order 6 64.9 -> 65.5.)
 template <int NP, int WPB>
 __device__ __forceinline__ void build_bf16_table(const float* __restrict__ D, Bf16x8Bits* ahi, Bf16x8Bits* alo) {
   using Sh = Shape<NP>;
@@ -74,7 +77,7 @@ __device__ __forceinline__ void fwd_f32s_staged_single(const FwdArgs<float>& p, 
   const uint32_t wave = threadIdx.x >> 6;
   float* stg = stg_all + wave * TILE;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = staged_worker<WPB>(bid, nblk, wave, p.ntiles);
+  uint32_t t = bid * WPB + wave;
   float raw[NREG];
   // a whole tile moves as pairs; a partial last tile word by word
   auto load_raw = [&](uint32_t tt) __attribute__((always_inline)) {
@@ -212,7 +215,7 @@ __device__ __forceinline__ void fwd_f32s_staged_multi(const FwdArgs<float>& p, u
   float* sg = su + RUN;
   const uint32_t nrun = (p.ntiles + TPI - 1) / TPI;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = staged_worker<WPB>(bid, nblk, wave, nrun);
+  uint32_t t = bid * WPB + wave;
   float raw[NREG], graw[NGR];
   auto run_elems = [&](uint32_t tt, uint32_t& e0, int& ng) __attribute__((always_inline)) {
     const uint32_t c0 = tt * (16 * TPI);
