@@ -240,7 +240,7 @@ __global__ __launch_bounds__(WAVE* WPB) __attribute__((amdgpu_waves_per_eu(adj_m
   };
   auto cols = [&](uint32_t t) __attribute__((always_inline)) {
     Cols c;
-    c.ncol = t < nrun ? min(16u, c_hi - (c_lo + t * step)) : 0u;
+    c.ncol = t < nrun ? cols_left(c_hi, c_lo + t * step, 16) : 0u;
     c.col0 = t < nrun ? c_lo + t * step : 0u;
     c.k0 = c.col0 / F;
     c.ne = c.ncol ? (c.col0 + c.ncol - 1u) / F - c.k0 + 1u : 0u;

@@ -83,7 +83,10 @@ __device__ __forceinline__ void store_stream(T* p, const T& v) { __builtin_nonte
 // ncols - c0) : 0, a second such expression with another c0 in the same
 // function let the compiler fold this one to `most` (it takes a no-wrap flag
 // of the guarded subtraction for a fact), and the loads then ran past the
-// arrays.  (A signed clamp to [0, most] becomes a vector median, and every
+// arrays.  A guard on the tile index instead (t < ntiles ? min(16, ncols - 16 t)
+// : 0, as the staged and chunk-register bodies have it) gives the compiler no
+// relation between ncols and 16 t to build that flag from; the bodies whose
+// stores depend on such a count use this form all the same.  (A signed clamp to [0, most] becomes a vector median, and every
 // buffer access built from it a loop over the lanes' descriptors.)
 __device__ __forceinline__ uint32_t cols_left(uint32_t ncols, uint32_t c0, uint32_t most) {
   return min(ncols, c0 + most) - min(ncols, c0);
