@@ -258,8 +258,10 @@ dg_status dg_volume_batched(const dg_group *groups, int32_t ngroups, int32_t F, 
  * tiles one loop iteration takes (per wave for the staged body, per workgroup
  * for the chunk-register body).  Variant 0 is the default that dg_volume and
  * dg_volume_f32s use, except in FP64 at Np = 56, where it is variant 1 up to
- * 2^18 columns (K F); the others are the autotuner's search space (the paper's
- * autotuning use case, Introduction and Section 3, applied to tile shapes).
+ * 2^18 columns (K F): these two give the same bits, so that an element's
+ * outputs do not depend on the size of its mesh.  The others are the
+ * autotuner's search space (the paper's autotuning use case, Introduction and
+ * Section 3, applied to tile shapes).
  * A single-group launch may run a variant's wave groups as workgroups of their
  * own; the description below is that of a batched launch.
  */

@@ -76,12 +76,20 @@ __device__ __forceinline__ uint32_t staged_worker(uint32_t bid, uint32_t nblk, u
 // The A-operand table of a staged body.  The buffer-range and multi-tile forms
 // request their first tile before it, so that the two latencies overlap (a fifth
 // of a small launch).
-template <int NP, int WPB>
+// PAIRS: k-steps 2 p, 2 p + 1 take nodes 8 p + 2 g, 8 p + 2 g + 1 (else 4 s + g).
+template <int NP, int WPB, bool PAIRS = false>
 __device__ __forceinline__ void build_fwd_table(const double* __restrict__ D, double* afr) {
   using Sh = Shape<NP>;
+  static_assert(!PAIRS || NP % 8 == 0, "whole pairs of k-steps");
   for (int e = threadIdx.x; e < fwd_table_doubles<NP>(); e += WAVE * WPB) {
     const int ts = e >> 6;
-    afr[e] = afrag_f64<NP>(D, ts / Sh::KS64, ts % Sh::KS64, e & 63);
+    int s = ts % Sh::KS64, l = e & 63;
+    if constexpr (PAIRS) {  // the entry of node j = 8 (s / 2) + 2 g + s % 2
+      const int j = 4 * (s & ~1) + 2 * (l >> 4) + (s & 1);
+      s = j >> 2;
+      l = (l & 15) + 16 * (j & 3);
+    }
+    afr[e] = afrag_f64<NP>(D, ts / Sh::KS64, s, l);
   }
   __syncthreads();
 }
@@ -219,6 +227,12 @@ __device__ __forceinline__ void fwd_f64_staged_single(const FwdArgs<double>& p, 
 // ranges (no branches around the memory operations), and the next tile is
 // staged at the end of an iteration, so that wait counts exactly the stores
 // issued after the loads instead of waiting for them too.
+// The k order is that of the direct body (dgvol_forward_direct.hpp), which
+// takes the smaller sizes: k-steps 2p, 2p + 1 take nodes 8p + 2g, 8p + 2g + 1,
+// so that an element's outputs do not depend on the size of its mesh.  It costs
+// nothing here (F = 3, 7.3e6 nodal values 62.2 -> 62.3 us, 2.9e7 208.7 -> 207.3);
+// node order 4 s + g in the direct body instead, which must then swap halves of
+// its 16-byte pairs, cost that body 1-5 % (3e5 values 7.7 -> 8.1 us).
 template <int NP, int WPB>
 __device__ __forceinline__ void fwd_f64_staged_early(const FwdArgs<double>& p, uint32_t bid, uint32_t nblk,
                                                      char* lds) {
@@ -258,7 +272,7 @@ __device__ __forceinline__ void fwd_f64_staged_early(const FwdArgs<double>& p, u
     wave_sync();
   };
   load_raw(t);
-  build_fwd_table<NP, WPB>(p.D, afr);
+  build_fwd_table<NP, WPB, true>(p.D, afr);
   stage();
   for (; t < p.ntiles; t += stride) {
     const uint32_t col0 = t * 16;
@@ -266,8 +280,7 @@ __device__ __forceinline__ void fwd_f64_staged_early(const FwdArgs<double>& p, u
     double b[Sh::KS64];
 #pragma unroll
     for (int s = 0; s < Sh::KS64; ++s) {
-      const int j = 4 * s + g;
-      b[s] = j < NP ? stg[n * LD + j] : 0.0;
+      b[s] = stg[n * LD + 8 * (s / 2) + 2 * g + s % 2];
     }
     const uint32_t col = col0 + n;
     const uint32_t k = (col < p.ncols ? col : 0u) / p.F;
