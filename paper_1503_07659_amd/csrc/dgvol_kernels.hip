@@ -128,6 +128,7 @@ struct VariantDesc {
   int wpb1;        // the same in a single-group launch
   int tiles1;
   int lds1;
+  bool spread;     // its body deals few runs of tiles to the workgroups first, not to one workgroup's waves
 };
 
 template <int NP, int BODY, int WPB, int TILES, int CLS>
@@ -136,11 +137,11 @@ static VariantDesc f64_desc() {
     using S = DirectShape<NP, WPB>;
     constexpr int W1 = S::UNITS, T1 = TILES / S::HALVES;
     return VariantDesc{reinterpret_cast<const void*>(fwd_f64_direct_kernel<NP, W1, T1>), BODY, WPB, TILES, CLS,
-                       f64_lds<NP, BODY, WPB, TILES>(), W1, T1, fwd_f64_direct_lds<NP, W1, T1>()};
+                       f64_lds<NP, BODY, WPB, TILES>(), W1, T1, fwd_f64_direct_lds<NP, W1, T1>(), true};
   } else {
     constexpr int lds = f64_lds<NP, BODY, WPB, TILES>();
     return VariantDesc{reinterpret_cast<const void*>(fwd_f64_kernel<NP, BODY, WPB, TILES>), BODY, WPB, TILES, CLS,
-                       lds, WPB, TILES, lds};
+                       lds, WPB, TILES, lds, true};
   }
 }
 
@@ -152,7 +153,7 @@ static bool variant_desc(int form, int Np, int v, VariantDesc* d) {
 #define DGVOL_VDESC32(NP, IDX, BODY, WPB, TILES, CLS)                                                    \
   case vkey(NP, IDX):                                                                                    \
     *d = VariantDesc{reinterpret_cast<const void*>(fwd_f32s_kernel<NP, BODY, WPB, TILES>), BODY, WPB, TILES, \
-                     CLS, f32s_lds<NP, BODY, WPB, TILES>(), WPB, TILES, f32s_lds<NP, BODY, WPB, TILES>()};  \
+                     CLS, f32s_lds<NP, BODY, WPB, TILES>(), WPB, TILES, f32s_lds<NP, BODY, WPB, TILES>(), false}; \
     return true;
   if (v < 0 || v >= 16) return false;
   if (form == DG_FORM_F64) {
@@ -201,6 +202,15 @@ static inline uint32_t workers_per_block(const VariantDesc& d) {
 static inline uint32_t units_per_step1(const VariantDesc& d) {
   return d.body != BODY_CHUNKREG ? (uint32_t)(d.wpb1 * d.tiles1) : (uint32_t)d.tiles1;
 }
+// ... and the tiles for which it launches one more workgroup, up to the resident count.
+// Where the body deals few runs of tiles to the workgroups first (staged_worker),
+// every run gets one, so that a small problem's runs sit on as many CUs as there
+// are.  The split-BF16 staged bodies fill a workgroup's waves first: a workgroup
+// a run would leave seven of eight with the operand table to build and no tile
+// (F = 3, order 5: 3e5 nodal values 9.7 us against 8.6, 1e6 9.2 against 8.3).
+static inline uint32_t units_per_block1(const VariantDesc& d) {
+  return d.spread ? (uint32_t)d.tiles1 : units_per_step1(d);
+}
 
 // The batched kernel of a launch class.
 static const void* batched_fn(int form, int cls) {
@@ -227,14 +237,12 @@ static inline int launch_class(const VariantDesc& d, bool by_class) {
   return d.wpb == 8 ? LCLASS_ALL8 : VCLASS_WAVE4;
 }
 
-// Persistent grid of a single-group launch of variant d over `ntiles` tiles: a
-// workgroup per loop step's tiles of one worker, up to the resident count (a
-// small problem's runs of tiles then sit on as many CUs as there are runs).
+// Persistent grid of a single-group launch of variant d over `ntiles` tiles.
 static uint32_t single_grid(const VariantDesc& d, uint32_t ntiles, int* err, uint32_t* resident) {
   const int cap = resident_blocks_fn(d.fn, WAVE * d.wpb1, d.lds1, err);
   if (*err != DG_OK) return 0;
   if (resident) *resident = (uint32_t)cap;
-  return std::min<uint32_t>(ceil_div(ntiles, (uint32_t)d.tiles1), (uint32_t)cap);
+  return std::min<uint32_t>(ceil_div(ntiles, units_per_block1(d)), (uint32_t)cap);
 }
 
 template <typename T>
@@ -777,7 +785,7 @@ dg_status dg_launch_shape_query(int32_t op, int32_t form, int32_t Np, int32_t va
       cap = (uint32_t)resident_blocks_fn(batched_fn(form, lc), sh.block, d.lds, &err);
     }
     if (err != DG_OK) return err;
-    sh.grid = std::min<uint32_t>(ceil_div(ntiles, single ? tiles : per), cap);
+    sh.grid = std::min<uint32_t>(ceil_div(ntiles, single ? units_per_block1(d) : per), cap);
     sh.lds_bytes = (uint32_t)lds;
     sh.resident = cap;
     sh.units = ntiles;

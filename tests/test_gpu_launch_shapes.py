@@ -1,0 +1,24 @@
+"""Launch shapes of small problems, as the library reports them (host queries of a GPU's occupancy)."""
+
+import pytest
+
+import oracle
+from paper_1503_07659_amd import dgvol
+
+pytestmark = pytest.mark.gpu
+
+ORDERS = range(1, 8)
+
+
+@pytest.mark.parametrize("N", ORDERS)
+def test_f32s_grid_has_no_workgroup_without_tiles(N):
+    """The split-BF16 staged bodies give neighbouring runs of tiles to a workgroup's waves, so a
+    workgroup past the last run would only build its operand table."""
+    Np, F = oracle.num_nodes(N), 3
+    for v in range(dgvol.variant_count(dgvol.FORM_F32S, Np)):
+        info = dgvol.variant_info(dgvol.FORM_F32S, Np, v)
+        per = info["tiles"] * (1 if info["body"] == 1 else info["waves"])
+        for K in (1, 7, 43, 300, 1431, 5000):
+            sh = dgvol.launch_shape(dgvol.OP_FORWARD, dgvol.FORM_F32S, Np, v, K, F)
+            ntiles = -(-K * F // 16)
+            assert sh["grid"] == min(-(-ntiles // per), sh["resident"]), (v, K, sh)
