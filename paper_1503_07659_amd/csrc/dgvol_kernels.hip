@@ -343,7 +343,9 @@ static dg_status adj_plan(int64_t K, int32_t F, AdjPlan* pl) {
     pl->units[0] = ceil_div((uint64_t)K * (uint64_t)F, 16);
     adj_workers(pl->units[0], (uint32_t)cap, adj_wpb(NP, true), &pl->grid[0], &pl->nworkers);
     const uint64_t nw = pl->nworkers;
-    pl->min_it[0] = (uint32_t)ceil_div((uint64_t)(K / nw) * (uint64_t)F, 16);
+    // (with fewer tiles than waves some have no run at all)
+    const bool idle = nw < (uint64_t)pl->grid[0] * adj_wpb(NP, true);
+    pl->min_it[0] = idle ? 0u : (uint32_t)ceil_div((uint64_t)(K / nw) * (uint64_t)F, 16);
     pl->max_it[0] = (uint32_t)ceil_div(ceil_div((uint64_t)K, nw) * (uint64_t)F, 16);
   }
   return DG_OK;

@@ -22,3 +22,14 @@ def test_f32s_grid_has_no_workgroup_without_tiles(N):
             sh = dgvol.launch_shape(dgvol.OP_FORWARD, dgvol.FORM_F32S, Np, v, K, F)
             ntiles = -(-K * F // 16)
             assert sh["grid"] == min(-(-ntiles // per), sh["resident"]), (v, K, sh)
+
+
+@pytest.mark.parametrize("N", range(1, 6))
+def test_adjoint_min_iters_counts_idle_waves(N):
+    """min_iters is that of the least-loaded wave: 0 where fewer 16-column tiles than waves are launched."""
+    Np = oracle.num_nodes(N)
+    for F in (1, 2, 3, 17):
+        for K in (1, 16, 160, 1600, 16000):
+            sh = dgvol.launch_shape(dgvol.OP_ADJOINT, dgvol.FORM_F64, Np, 0, K, F)
+            if sh["units"] < sh["grid"] * (sh["block"] // 64):
+                assert sh["min_iters"] == 0, (K, F, sh)
