@@ -25,11 +25,15 @@ launch modes -- and keeps the fastest, so a tuned batch is never slower than
 the default one as measured.
 
 Results are cached in a JSON file (``$DGVOL_AUTOTUNE_CACHE``, default
-``~/.cache/dgvol/autotune.json``) keyed by the GPU architecture and the
-library ABI version; an unreadable, corrupt or foreign cache is ignored and
-rewritten.  Tuning needs a GPU; looking up the cache does not.
+``~/.cache/dgvol/autotune.json``) keyed by the GPU architecture, the library
+ABI version and the library file's contents: times measured on one build say
+nothing of another, whose kernels may differ behind the same variant numbers.
+An unreadable, corrupt or foreign cache is ignored and rewritten.  Tuning needs
+a GPU; looking up the cache does not.
 """
 
+import functools
+import hashlib
 import json
 import os
 import tempfile
@@ -49,11 +53,17 @@ def cache_path():
     return os.environ.get("DGVOL_AUTOTUNE_CACHE", DEFAULT_CACHE)
 
 
+@functools.lru_cache(maxsize=None)
+def _library_revision(path):
+    with open(path, "rb") as fh:
+        return hashlib.sha256(fh.read()).hexdigest()[:16]
+
+
 def device_key(device=None):
-    """Cache namespace: architecture of the device and ABI version of the library."""
+    """Cache namespace: architecture of the device, ABI version and contents of the library."""
     props = torch.cuda.get_device_properties(device or torch.cuda.current_device())
     arch = getattr(props, "gcnArchName", props.name).split(":")[0]
-    return f"{arch}/abi{dgvol.load_library().dg_abi_version()}"
+    return f"{arch}/abi{dgvol.load_library().dg_abi_version()}/{_library_revision(dgvol.LIB_PATH)}"
 
 
 def entry_key(form, Np, F):
