@@ -73,6 +73,10 @@ typedef int32_t dg_status;
 /* Variant (launch shape) selection: DG_VARIANT_AUTO is the library's default. */
 #define DG_VARIANT_AUTO (-1)
 
+/* Largest call (nodal values of all its groups) in which DG_VARIANT_AUTO selects variant 1 at Np = 56
+ * in FP64: 240 000 columns of that order (see dg_variant_info). */
+#define DG_ORDER5_DIRECT_MAX_VALUES 13440000
+
 #define DG_MAX_GROUPS 16
 
 /* Version of this interface (DGVOL_ABI_VERSION of the built library).
@@ -258,8 +262,9 @@ dg_status dg_volume_batched(const dg_group *groups, int32_t ngroups, int32_t F, 
  * tiles one loop iteration takes (per wave for the staged body, per workgroup
  * for the chunk-register body).  Variant 0 is the default that dg_volume and
  * dg_volume_f32s use, except in FP64 at Np = 56, where it is variant 1 up to
- * 2^18 columns (K F): these two give the same bits, so that an element's
- * outputs do not depend on the size of its mesh.  The others are the
+ * DG_ORDER5_DIRECT_MAX_VALUES nodal values (K F Np; in a batch, of all groups
+ * together): these two give the same bits, so that an element's outputs do not
+ * depend on the size of its mesh or on its batch.  The others are the
  * autotuner's search space (the paper's autotuning use case, Introduction and
  * Section 3, applied to tile shapes).
  * A single-group launch may run a variant's wave groups as workgroups of their

@@ -167,17 +167,21 @@ static bool variant_desc(int form, int Np, int v, VariantDesc* d) {
 #undef DGVOL_VDESC32
 }
 
-// The variant DG_VARIANT_AUTO selects, for a group on its own and in a batch: the first of
-// its list, except for FP64 at order 5 up to 2^18 columns, where the direct
-// body (variant 1) takes over.  Its stores are 128-byte runs that straddle
-// cache lines: while the three planes stay in the 256 MB memory-side cache
-// they cost nothing and its short start (D straight into registers) wins:
-// 20.0 -> 10.5 us at 150 thousand nodal values, 34.9 -> 27.5 us at 3e6, 83.8
-// -> 78.7 us at 1e7.  Past it the staged body's full-line streaming stores
-// win (2.2e7: 165.7 against 171.3 us; 9e7: 631 against 678 us).
-constexpr uint64_t DIRECT56_MAX_COLS = 1u << 18;
-static int auto_variant(int form, int Np, uint64_t ncols) {
-  return form == DG_FORM_F64 && Np == 56 && ncols <= DIRECT56_MAX_COLS ? 1 : 0;
+// The variant DG_VARIANT_AUTO selects: the first of its list, except for FP64
+// at order 5 in a call (all groups of a batch together) of up to
+// DG_ORDER5_DIRECT_MAX_VALUES nodal values, 240 thousand columns of order 5,
+// where the direct body (variant 1; the same bits) takes over.  Its stores are
+// 128-byte runs that straddle cache lines: while most of the three planes stays
+// in the 256 MB memory-side cache they cost little and its short start (D
+// straight into registers) wins; past it the staged body's full-line streaming
+// stores do.  Staged -> direct, F = 3, columns of order 5 alone, on the same
+// buffers each call / on three sets in turn: 5 thousand 12.6 -> 7.7 us / 12.3 ->
+// 7.7; 1.5e5 73.7 -> 69.1 / 75.2 -> 70.0; 2.3e5 107 -> 104 / 112 -> 103; 2.46e5
+// 111 -> 110 / 112 -> 110; 2.62e5 113 -> 117 / 119 -> 120; 5.2e5 209 -> 228 / 218
+// -> 228.  In batches of orders 1-7: 3.9e6 nodal values in all 47 -> 40, 9.5e6
+// 104 -> 104, 1.7e7 154 -> 160, 5.9e7 680 -> 681.
+static int auto_variant(int form, int Np, uint64_t values) {
+  return form == DG_FORM_F64 && Np == 56 && values <= DG_ORDER5_DIRECT_MAX_VALUES ? 1 : 0;
 }
 
 static int variant_count(int form, int Np) {
@@ -562,7 +566,7 @@ dg_status dg_volume_variant(int32_t form, int32_t variant, const void* D, const 
   if (st != DG_OK) return st;
   if (form != DG_FORM_F64 && form != DG_FORM_F32S) return DG_EUNSUPPORTED;
   VariantDesc d;
-  const int v = variant == DG_VARIANT_AUTO ? auto_variant(form, Np, (uint64_t)K * (uint64_t)F) : variant;
+  const int v = variant == DG_VARIANT_AUTO ? auto_variant(form, Np, (uint64_t)K * (uint64_t)F * (uint64_t)Np) : variant;
   if (!variant_desc(form, Np, v, &d)) return DG_EUNSUPPORTED;
   if (noop) return DG_OK;
   const uintptr_t word = form == DG_FORM_F64 ? 8 : 4;
@@ -673,12 +677,14 @@ dg_status dg_volume_batched(const dg_group* groups, int32_t ngroups, int32_t F, 
   VariantDesc desc[DG_MAX_GROUPS];
   bool live[DG_MAX_GROUPS];
   int32_t variant[DG_MAX_GROUPS];
+  uint64_t values = 0;  // nodal values of the call (of a group that is refused below: any number)
+  for (int i = 0; i < ngroups; ++i) values += (uint64_t)groups[i].K * (uint64_t)F * (uint64_t)groups[i].Np;
   for (int i = 0; i < ngroups; ++i) {
     const dg_group& gr = groups[i];
     bool noop = false;
     const dg_status st = check_common(gr.K, gr.Np, F, &noop);
     if (st != DG_OK) return st;
-    variant[i] = gr.variant == DG_VARIANT_AUTO ? auto_variant(form, gr.Np, (uint64_t)gr.K * (uint64_t)F) : gr.variant;
+    variant[i] = gr.variant == DG_VARIANT_AUTO ? auto_variant(form, gr.Np, values) : gr.variant;
     if (!variant_desc(form, gr.Np, variant[i], &desc[i])) return DG_EUNSUPPORTED;
     live[i] = !noop;
     if (noop) continue;
@@ -770,7 +776,7 @@ dg_status dg_launch_shape_query(int32_t op, int32_t form, int32_t Np, int32_t va
   dg_launch_shape sh{};
   if (op == DG_OP_FORWARD || op == DG_OP_BATCHED || op == DG_OP_BATCHED_BY_CLASS) {
     VariantDesc d;
-    const int v = variant == DG_VARIANT_AUTO ? auto_variant(form, Np, (uint64_t)K * (uint64_t)F) : variant;
+    const int v = variant == DG_VARIANT_AUTO ? auto_variant(form, Np, (uint64_t)K * (uint64_t)F * (uint64_t)Np) : variant;
     if (!variant_desc(form, Np, v, &d)) return DG_EUNSUPPORTED;
     const uint32_t ntiles = ceil_div((uint64_t)K * (uint64_t)F, 16);
     const bool single = op == DG_OP_FORWARD;

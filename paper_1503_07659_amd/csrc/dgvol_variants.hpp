@@ -3,8 +3,8 @@
 // many waves a workgroup has, and how many 16-column tiles one loop iteration
 // takes (per wave for the staged body, per workgroup for the chunk-register
 // body).  Variant 0 of each list is the library's default (order 5 in FP64:
-// variant 1 up to a size, see auto_variant); the others are the search space of the autotuner (the paper's autotuning use case, here
-// applied to tile shapes).  A variant's index is its position in its list and
+// variant 1 up to a size, see auto_variant); the others are the search space of
+// the autotuner (the paper's autotuning use case, here applied to tile shapes).  A variant's index is its position in its list and
 // is part of the ABI (dg_volume_variant, dg_group.variant).
 //
 // The mixed-order batched launch runs each group's variant inside one of a few

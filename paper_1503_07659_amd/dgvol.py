@@ -39,6 +39,8 @@ BODY_STAGED = 0
 BODY_CHUNKREG = 1
 BODY_STAGED_LEAN = 2
 VARIANT_AUTO = -1
+# nodal values of a call up to which VARIANT_AUTO selects variant 1 at Np = 56 in FP64
+ORDER5_DIRECT_MAX_VALUES = 13440000
 MAX_GROUPS = 16
 
 OP_FORWARD = 0

@@ -1,5 +1,5 @@
-"""FP64 forward at order 5, where two bodies serve the sizes: up to 2^18 columns (K F) the body that
-stores from its accumulators, beyond it the staged one.  An element's outputs must not depend on the
+"""FP64 forward at order 5, where two bodies serve the sizes: up to 240 000 columns (K F; in a batch, as
+many nodal values in all) the body that stores from its accumulators, beyond it the staged one.  An element's outputs must not depend on the
 mesh it sits in, so the two sum in the same order: the same bits for a mesh in one call, in pieces,
 and in a batch, on both sides of the edge.  Elements at both ends are also checked against the oracle
 (the suite's 1e-12 pair)."""
@@ -15,7 +15,7 @@ from parity import check_planes, forward_cond
 pytestmark = pytest.mark.gpu
 
 N, NP = 5, 56
-EDGE = 1 << 18
+EDGE = dgvol.ORDER5_DIRECT_MAX_VALUES // NP
 
 
 def _inputs(K, F, seed):
@@ -49,3 +49,25 @@ def test_default_at_the_edge():
     for lo, hi in ((0, 200), (K - 200, K)):
         check_planes(whole[:, lo:hi].cpu().numpy(), oracle.volume(Dh, Gh[lo:hi], uh[lo:hi]),
                      forward_cond(Dh, Gh[lo:hi], uh[lo:hi]))
+
+
+@pytest.mark.parametrize("op", [dgvol.OP_FORWARD, dgvol.OP_BATCHED])
+@pytest.mark.parametrize("F", [1, 16])
+def test_default_variant_at_the_edge(op, F):
+    assert EDGE * NP == dgvol.ORDER5_DIRECT_MAX_VALUES and EDGE % 16 == 0
+    shape = lambda v, K: dgvol.launch_shape(op, dgvol.FORM_F64, NP, v, K, F)  # noqa: E731
+    for K, variant in ((EDGE // F, 1), (EDGE // F + 1, 0)):
+        assert shape(0, K) != shape(1, K)
+        assert shape(dgvol.VARIANT_AUTO, K) == shape(variant, K)
+
+
+def test_batch_counts_all_its_groups():
+    """A batch past the limit runs order 5 staged whatever its own share; the same bits either way."""
+    print("[gpu-case] order-5 default in batches", flush=True)
+    _, small = _inputs(3000, 3, 9300)
+    _, rest = _inputs(EDGE, 1, 9200)
+    (alone,) = dgvol.dg_volume_batched([small])
+    rest3 = (rest[0], rest[1][:EDGE // 3], rest[2].view(EDGE // 3, 3, NP))
+    both = dgvol.dg_volume_batched([small, rest3])
+    assert torch.equal(alone, both[0])
+    assert torch.equal(both[1], dgvol.dg_volume(*rest3))
