@@ -180,15 +180,29 @@ def lookup(form, Np, F, device=None, cache=None, tune_missing=True):
 
 def plan(groups, form=dgvol.FORM_F64, tune_missing=True, by_class=False):
     """Per-group variants and measured tile costs for dg_volume_batched (in the given launch mode)
-    from the tuning cache."""
+    from the tuning cache.
+
+    The entries are measured on large problems.  Where the library's default depends on the size of
+    the call (FP64 at Np = 56), a call below that size keeps the default, with the measured cost of
+    the variant it stands for."""
     variants, costs = [], []
     data = load_cache()
     vk, ck = ("by_class_variant", "by_class_tile_cost_s") if by_class else ("variant", "tile_cost_s")
+    tk = "by_class_candidates_s_per_tile" if by_class else "candidates_s_per_tile"
+    small = form == dgvol.FORM_F64 and sum(u.numel() for _, _, u in groups) <= dgvol.ORDER5_DIRECT_MAX_VALUES
     for D, G, u in groups:
         K, F, Np = u.shape
         e = lookup(form, Np, F, device=u.device, cache=data, tune_missing=tune_missing)
-        variants.append(dgvol.VARIANT_AUTO if e is None else e[vk])
-        costs.append(0.0 if e is None else e[ck])
+        if e is None:
+            variants.append(dgvol.VARIANT_AUTO)
+            costs.append(0.0)
+        elif small and Np == 56:
+            cost = e[tk].get("1") if isinstance(e.get(tk), dict) else None  # (VARIANT_AUTO is variant 1 here)
+            variants.append(dgvol.VARIANT_AUTO)
+            costs.append(cost if isinstance(cost, float) and cost > 0 else 0.0)
+        else:
+            variants.append(e[vk])
+            costs.append(e[ck])
     return variants, costs
 
 
@@ -204,7 +218,7 @@ def plan_batch(groups, form=dgvol.FORM_F64, outs=None, reps=20, tune_missing=Tru
     by_class, candidates).
 
     Candidates, each in both launch modes (one launch for all 8-wave groups, and one launch per
-    variant class): the library default (variant 0, estimated costs), the per-group tuned
+    variant class): the library default (VARIANT_AUTO, estimated costs), the per-group tuned
     variants with their measured costs, and the tuned variants with the estimated costs.  Each
     is timed on the actual groups, in five alternating rounds; the default is kept unless a
     candidate is more than PLAN_MARGIN faster.  The result is cached under the batch's shapes;

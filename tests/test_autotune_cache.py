@@ -40,3 +40,20 @@ def test_cache_belongs_to_one_build_of_the_library(gpu, monkeypatch, tmp_path):
     monkeypatch.setattr(dgvol, "LIB_PATH", other2)
     assert autotune.device_key(gpu) != key
     assert autotune.lookup(dgvol.FORM_F64, 35, 3, device=gpu, tune_missing=False) is None
+
+
+@pytest.mark.parametrize("by_class,cost", [(False, 2e-7), (True, 3e-7)])
+def test_plan_keeps_the_default_of_small_calls(gpu, by_class, cost):
+    """FP64 order 5: the variant tuned on a large problem (0 here) is not forced on a call below the
+    size at which the library's default changes."""
+    autotune.save_cache({autotune.device_key(gpu): {autotune.entry_key(dgvol.FORM_F64, Np, 3): ENTRY for Np in (35, 56)}})
+    group = lambda Np, K: (None, None, types.SimpleNamespace(shape=(K, 3, Np), device=gpu, numel=lambda: K * 3 * Np))  # noqa: E731
+    edge = dgvol.ORDER5_DIRECT_MAX_VALUES // (3 * 56)
+    plan = lambda *gr: autotune.plan(list(gr), tune_missing=False, by_class=by_class)  # noqa: E731
+    assert plan(group(56, edge)) == ([dgvol.VARIANT_AUTO], [cost])
+    assert plan(group(56, edge + 1)) == ([0], [1e-7])
+    assert plan(group(56, edge), group(35, 1)) == ([0, 0], [1e-7, 1e-7])  # the call as a whole is past it
+    assert plan(group(56, 100), group(35, 1)) == ([dgvol.VARIANT_AUTO, 0], [cost, 1e-7])
+    broken = dict(ENTRY, candidates_s_per_tile=["x"], by_class_candidates_s_per_tile={"1": "y"})
+    autotune.save_cache({autotune.device_key(gpu): {autotune.entry_key(dgvol.FORM_F64, 56, 3): broken}})
+    assert plan(group(56, 100)) == ([dgvol.VARIANT_AUTO], [0.0])
