@@ -143,13 +143,22 @@ def _raise_on(status, what):
         raise DGVolError(status, f"{what}: {strerror(status)}")
 
 
+def _stream_handle(index):
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# the same handle without building a Stream object (a microsecond of a small call); torch does not
+# document it, so its absence is no error
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_handle)
+
+
 def _call(fn, what, dev, *args):
     """Run a library entry point on `dev` (the device of a checked tensor) and torch's current stream of it."""
     if torch.cuda.current_device() == dev.index:
-        st = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+        st = fn(*args, _raw_stream(dev.index))
     else:
         with torch.cuda.device(dev):
-            st = fn(*args, torch._C._cuda_getCurrentRawStream(dev.index))
+            st = fn(*args, _raw_stream(dev.index))
     if st != DG_OK:
         _raise_on(st, what)
 
