@@ -292,7 +292,14 @@ __global__ __launch_bounds__(WAVE* WPB) __attribute__((amdgpu_waves_per_eu(adj_m
     for (int ch = 0; ch < NCH; ++ch)
       if (ch == 0 || !AHEAD1) load_go(r, ch);
   }
-  const float invF = 1.0f / (float)F;
+  // From Np = 20 in a scalar register: in a vector register it was the one that
+  // spilled at Np = 56, and its reload in the loop waited for every memory
+  // operation in flight (F = 3, 2e7 nodal values 269 -> 262 us, gu alone 156 ->
+  // 153).  At Np = 10 the register saved let a seventh wave in, which made gu
+  // alone slower (135 -> 137).
+  float invF = 1.0f / (float)F;
+  if constexpr (NP >= 20)
+    invF = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(opaque(__builtin_bit_cast(int, invF))));
   for (uint32_t t = 0; t < nrun; ++t) {
     const Cols nxt = cols(t + 1);
 #pragma unroll
