@@ -17,9 +17,12 @@
 //     (registers Q below) whose products run as v_mfma_f64_4x4x4f64 (four
 //     4 x 4 blocks, 16 cycles against 64 for a 16 x 16 tile);
 //   * loads run two k-steps ahead (u one, each register reloaded right after
-//     its products, where registers are short: Np >= 56); the 9 geometric factors of a column come as
-//     one load (lane n of its 16-lane row takes factor n) and are handed to
-//     the row by DPP broadcasts;
+//     its products, where registers are short: Np >= 84, and Np = 56 with the
+//     rows split over two workgroups, where the second step's u spilled and
+//     every other step waited for all loads in flight: 1e6 nodal values 20.9 ->
+//     20.0 us, 1.8e6 25.8 -> 24.1); the 9 geometric factors of a column come as
+//     one load (lane n of its 16-lane row takes factor n) and are handed to the
+//     row by DPP broadcasts;
 //   * the waves of a workgroup share its column range; a wave holds every
 //     output (up to Np = 35) or those of a group of rows (Np = 56: 2 groups,
 //     84: 4, 120: 8) in its accumulators.  Groups of rows, not directions:
@@ -119,7 +122,7 @@ __device__ __forceinline__ void gd_static_for(Fn&& fn) {
 
 // A wave's share: row group rg_ (LAST: of the last kind), directions a0 .. a0 + ND - 1, over column
 // slice `slice` of the part.
-template <int NP, bool LAST, int ND>
+template <int NP, bool LAST, int ND, int RS>
 __device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t slice, int rg_, int a0, double* lds) {
   using S = GdShape<NP>;
   constexpr int NF = S::NF, NQ = S::NQ;
@@ -134,7 +137,7 @@ __device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t
   constexpr int NG = NR + (X ? 1 : 0) + NRQ;  // gout registers per plane: tiles, extra tile, quads
   constexpr int NU = NF + NQ;                 // u registers: tiles, quads
   constexpr int DEPTH = 2;            // gout register sets
-  constexpr int UD = NP >= 84 ? 1 : DEPTH;  // u register sets
+  constexpr int UD = NP >= 84 || (NP == 56 && ND == 3 && RS == 2) ? 1 : DEPTH;  // u register sets
   const int lane = threadIdx.x & 63;
   const int n = lane & 15, g = lane >> 4;
 
@@ -473,9 +476,9 @@ void gd_partial_kernel(GdArgs p) {
   double* mine = lds + (S::SLICES > 1 ? rg % (S::NRG / RS) * S::lds_group(ND) : 0);
   // (both kinds run the same number of workgroup barriers)
   if (S::NRG > 1 && rg + 1 < S::NRG)
-    gd_role<NP, S::NRG == 1, ND>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);
+    gd_role<NP, S::NRG == 1, ND, RS>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);
   else
-    gd_role<NP, true, ND>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);
+    gd_role<NP, true, ND, RS>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);
 }
 
 // gD[x] = sum over parts of work[part][x], x < n, in a fixed order.

@@ -422,8 +422,8 @@ static dg_status launch_gd_f64(const double* G, const double* u, const double* g
   // From Np = 56, rows over two workgroups while the parts alone leave CUs idle
   // (fewer than MAXPART = 256), and then at most 128 parts: 256 workgroups.
   // One workgroup a part from 129 parts up left 116 of 256 CUs idle at 140
-  // parts.  F = 3, unsplit -> split: order 5, 1e6 nodal values 24.0 -> 20.5 us,
-  // 1.8e6 26.5 -> 25.8; order 6, 1.4e6 37.8 -> 27.9, 2.5e6 41.5 -> 37.9; order 7,
+  // parts.  F = 3, unsplit -> split: order 5, 1e6 nodal values 24.0 -> 20.0 us,
+  // 1.8e6 26.5 -> 24.1; order 6, 1.4e6 37.8 -> 27.9, 2.5e6 41.5 -> 37.9; order 7,
   // 2e6 66.3 -> 45.8, 3.6e6 76.5 -> 71.3.  At 256 parts the chip is full without.
   const bool split_rows = NP >= 56 && npart < S::MAXPART;
   npart = std::min<uint32_t>(npart, split_rows ? 128u : S::MAXPART);

@@ -48,3 +48,11 @@ def test_no_spills(kernels, prefix):
     mine = {k: v for k, v in kernels.items() if re.match(rf"_ZN5dgvol\d+{prefix}I", k)}
     assert mine
     assert not {k: v for k, v in mine.items() if v}
+
+
+def test_no_spills_in_the_loops_of_the_cotangent_of_d(kernels):
+    """The whole-part forms at Np = 56 and 84 keep 1 and 3 registers in scratch across the loop (stored
+    before it, read after it); the others must not spill at all."""
+    mine = {re.match(r"_ZN5dgvol\d+gd_partial_kernelILi(\d+)ELi(\d)ELi(\d)E", k): v for k, v in kernels.items()}
+    spilled = {tuple(int(x) for x in m.groups()): v for m, v in mine.items() if m and v}
+    assert set(spilled) <= {(56, 3, 1), (84, 3, 1)}, spilled
