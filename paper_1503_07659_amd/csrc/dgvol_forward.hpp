@@ -73,9 +73,7 @@ __device__ __forceinline__ uint32_t staged_worker(uint32_t bid, uint32_t nblk, u
   return nrun >= nblk * WPB ? bid * WPB + wave : wave * nblk + bid;
 }
 
-// The A-operand table of a staged body.  The buffer-range and multi-tile forms
-// request their first tile before it, so that the two latencies overlap (a fifth
-// of a small launch).
+// The A-operand table of a staged body.
 // PAIRS: k-steps 2 p, 2 p + 1 take nodes 8 p + 2 g, 8 p + 2 g + 1 (else 4 s + g).
 template <int NP, int WPB, bool PAIRS = false>
 __device__ __forceinline__ void build_fwd_table(const double* __restrict__ D, double* afr) {
@@ -365,7 +363,12 @@ __device__ __forceinline__ void fwd_f64_staged_multi(const FwdArgs<double>& p, u
   double* sg = su + RUN;
   const uint32_t nrun = (p.ntiles + TPI - 1) / TPI;
   const uint32_t stride = nblk * WPB;
-  uint32_t t = staged_worker<WPB>(bid, nblk, wave, nrun);
+  // Close to a run a wave, runs spread over the workgroups cost more than
+  // neighbouring ones: order 2 from three quarters on (F = 3, 1e6 nodal values 8.6
+  // us against 8.2), order 1 nearer to it (F = 1, 8e5 7.0 against 7.4, 1e6 8.1
+  // against 7.8); order 3 at three quarters 8.9 against 9.6.
+  const bool near = (uint64_t)nrun * 8 > (uint64_t)stride * (NP == 10 ? 6 : 7);
+  uint32_t t = near ? bid * WPB + wave : staged_worker<WPB>(bid, nblk, wave, nrun);
   double raw[NRAW], graw[NGR];
   // first element of the run and the number of its G words
   auto run_elems = [&](uint32_t tt, uint32_t& e0, int& ng) __attribute__((always_inline)) {
@@ -403,8 +406,14 @@ __device__ __forceinline__ void fwd_f64_staged_multi(const FwdArgs<double>& p, u
     }
     wave_sync();
   };
-  load_run(t);
+  // The first run is requested before the operand table is built where the waves
+  // take several, after it where most take one: there the table's own reads then
+  // wait for it (order 2, F = 1, 1e5 nodal values 4.7 us, 5.5 with the request
+  // first; order 3, 1.35e6 14.1 against 14.5, 2e6 15.7 against 15.0).
+  const bool several = (uint64_t)nrun * 4 > (uint64_t)stride * 5;
+  if (several) load_run(t);
   build_fwd_table<NP, WPB>(p.D, afr);
+  if (!several) load_run(t);
   stage();
   for (; t < nrun; t += stride) {
     const uint32_t col0 = t * (16 * TPI);

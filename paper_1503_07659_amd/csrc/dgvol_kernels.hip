@@ -137,11 +137,11 @@ static VariantDesc f64_desc() {
     using S = DirectShape<NP, WPB>;
     constexpr int W1 = S::UNITS, T1 = TILES / S::HALVES;
     return VariantDesc{reinterpret_cast<const void*>(fwd_f64_direct_kernel<NP, W1, T1>), BODY, WPB, TILES, CLS,
-                       f64_lds<NP, BODY, WPB, TILES>(), W1, T1, fwd_f64_direct_lds<NP, W1, T1>(), true};
+                       f64_lds<NP, BODY, WPB, TILES>(), W1, T1, fwd_f64_direct_lds<NP, W1, T1>(), false};
   } else {
     constexpr int lds = f64_lds<NP, BODY, WPB, TILES>();
     return VariantDesc{reinterpret_cast<const void*>(fwd_f64_kernel<NP, BODY, WPB, TILES>), BODY, WPB, TILES, CLS,
-                       lds, WPB, TILES, lds, true};
+                       lds, WPB, TILES, lds, BODY != BODY_CHUNKREG};
   }
 }
 
@@ -206,14 +206,22 @@ static inline uint32_t workers_per_block(const VariantDesc& d) {
 static inline uint32_t units_per_step1(const VariantDesc& d) {
   return d.body != BODY_CHUNKREG ? (uint32_t)(d.wpb1 * d.tiles1) : (uint32_t)d.tiles1;
 }
-// ... and the tiles for which it launches one more workgroup, up to the resident count.
-// Where the body deals few runs of tiles to the workgroups first (staged_worker),
-// every run gets one, so that a small problem's runs sit on as many CUs as there
-// are.  The split-BF16 staged bodies fill a workgroup's waves first: a workgroup
+// ... and the workgroups it launches for `ntiles` tiles, at most `cap` of them.
+// Where the body deals few runs of tiles to the workgroups first (staged_worker):
+// a workgroup a run up to one on each of the 256 CUs, beyond that whole rounds of
+// workgroups over the CUs, of which the runs then fill the last.  One a run up to
+// the resident count put two workgroups on a CU whose waves had mostly no run to
+// share the table's cost (order 1, F = 1, 3e5 nodal values 5.7 us, now 5.0; order
+// 2, 5e5 6.3, now 5.6); one per its waves' runs leaves CUs empty (4.9 at 2e4, now
+// 4.1) or unevenly loaded (order 1, 6e5 7.4, now 6.6).
+// The split-BF16 staged bodies fill a workgroup's waves first: a workgroup
 // a run would leave seven of eight with the operand table to build and no tile
 // (F = 3, order 5: 3e5 nodal values 9.7 us against 8.6, 1e6 9.2 against 8.3).
-static inline uint32_t units_per_block1(const VariantDesc& d) {
-  return d.spread ? (uint32_t)d.tiles1 : units_per_step1(d);
+static inline uint32_t single_blocks(const VariantDesc& d, uint32_t ntiles, uint32_t cap) {
+  if (!d.spread) return std::min<uint32_t>(ceil_div(ntiles, units_per_step1(d)), cap);
+  constexpr uint32_t CUS = 256;
+  const uint32_t runs = ceil_div(ntiles, (uint32_t)d.tiles1);
+  return std::min(std::min<uint32_t>(runs, CUS * ceil_div(runs, CUS * (uint32_t)d.wpb1)), cap);
 }
 
 // The batched kernel of a launch class.
@@ -246,7 +254,7 @@ static uint32_t single_grid(const VariantDesc& d, uint32_t ntiles, int* err, uin
   const int cap = resident_blocks_fn(d.fn, WAVE * d.wpb1, d.lds1, err);
   if (*err != DG_OK) return 0;
   if (resident) *resident = (uint32_t)cap;
-  return std::min<uint32_t>(ceil_div(ntiles, units_per_block1(d)), (uint32_t)cap);
+  return single_blocks(d, ntiles, (uint32_t)cap);
 }
 
 template <typename T>
@@ -797,7 +805,7 @@ dg_status dg_launch_shape_query(int32_t op, int32_t form, int32_t Np, int32_t va
       cap = (uint32_t)resident_blocks_fn(batched_fn(form, lc), sh.block, d.lds, &err);
     }
     if (err != DG_OK) return err;
-    sh.grid = std::min<uint32_t>(ceil_div(ntiles, single ? units_per_block1(d) : per), cap);
+    sh.grid = single ? single_blocks(d, ntiles, cap) : std::min<uint32_t>(ceil_div(ntiles, per), cap);
     sh.lds_bytes = (uint32_t)lds;
     sh.resident = cap;
     sh.units = ntiles;
