@@ -314,13 +314,36 @@ struct AdjPlan {
   uint32_t max_it[2];
 };
 
-// Grid and workers (waves with a run of tiles) of an adjoint kernel below Np =
-// 84 with `cap` resident workgroups: one worker per tile while there are waves
-// for them, in as many workgroups as tiles (at order 5, 335 tiles, one 8-wave
-// workgroup per 8 tiles used 42 of 256 CUs).
+// Grid and workers (waves with a run of tiles) of an adjoint kernel below Np = 84 with `cap`
+// resident workgroups of `wpb` waves: one worker per tile while there are waves for them,
+// over as many CUs as there are workers (at order 5, 335 tiles, one 8-wave workgroup per 8
+// tiles used 42 of 256), in whole rounds of workgroups over the 256 CUs.
+static uint32_t adj_grid(uint32_t workers, uint32_t cap, uint32_t wpb) {
+  constexpr uint32_t CUS = 256;
+  return std::min(std::min(workers, CUS * ((workers + CUS * wpb - 1u) / (CUS * wpb))), cap);
+}
+// gu alone: tiles in turn
 static void adj_workers(uint32_t tiles, uint32_t cap, uint32_t wpb, uint32_t* grid, uint32_t* workers) {
-  *grid = std::min<uint32_t>(tiles, cap);
-  *workers = std::min<uint32_t>(tiles, *grid * wpb);
+  *workers = std::min<uint32_t>(tiles, cap * wpb);
+  *grid = adj_grid(*workers, cap, wpb);
+}
+// gu and gG: runs of whole elements.  A run that ends in a tile's first columns
+// costs that whole tile: with one worker per tile, 19 elements of one column (order 3, K
+// = 55461) are two tiles for every worker, three workers a SIMD.  Where fewer workers whose
+// runs fill those tiles make the busiest SIMD's load clearly smaller, they are taken (this
+// case 17.1 -> 14.4 us; order 5, K = 4436, F = 5 46.8 -> 29.0).
+static void adj_runs(uint32_t K, uint32_t F, uint32_t cap, uint32_t wpb, uint32_t* grid, uint32_t* workers) {
+  // (32-bit divisions, K F < 2^31: this runs on every call)
+  constexpr uint32_t SIMDS = 1024;
+  const uint32_t nw = std::min((K * F + 15u) / 16u, cap * wpb);
+  const uint32_t q = K / nw, r = K - q * nw;  // r workers take q + 1 elements, the others q
+  const uint32_t tq = (q * F + 15u) / 16u, longest = r ? ((q + 1u) * F + 15u) / 16u : tq;
+  const uint32_t e = std::max(longest * 16u / F, 1u), fuller = (K + e - 1u) / e;
+  // tiles of the busiest SIMD, times nw
+  const uint64_t load = (uint64_t)((nw + SIMDS - 1u) / SIMDS) * ((uint64_t)(nw - r) * tq + (uint64_t)r * longest);
+  const uint64_t load_fuller = (uint64_t)((fuller + SIMDS - 1u) / SIMDS) * longest * nw;
+  *workers = load_fuller * 10 <= load * 9 ? fuller : nw;
+  *grid = adj_grid(*workers, cap, wpb);
 }
 
 template <int NP>
@@ -357,7 +380,7 @@ static dg_status adj_plan(int64_t K, int32_t F, AdjPlan* pl) {
     pl->workers[0] = adj_wpb(NP, true);
     // runs of whole elements per wave, taken as 16-column tiles
     pl->units[0] = ceil_div((uint64_t)K * (uint64_t)F, 16);
-    adj_workers(pl->units[0], (uint32_t)cap, adj_wpb(NP, true), &pl->grid[0], &pl->nworkers);
+    adj_runs((uint32_t)K, (uint32_t)F, (uint32_t)cap, adj_wpb(NP, true), &pl->grid[0], &pl->nworkers);
     const uint64_t nw = pl->nworkers;
     // (with fewer tiles than waves some have no run at all)
     const bool idle = nw < (uint64_t)pl->grid[0] * adj_wpb(NP, true);
