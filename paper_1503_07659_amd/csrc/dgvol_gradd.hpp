@@ -86,14 +86,18 @@ struct GdShape {
   static constexpr int acc(bool last, int nd) {
     return nd * nt(last) * (4 * NF + NQ) + (xt(last) >= 0 ? 4 * NF + NQ : 0) + (rq(last) ? nd * (NQ * NF + NQ) : 0);
   }
-  // of them, those that pass through LDS at a time (Np = 84: all would be 166 KiB)
-  static constexpr int passes(int nd) { return NP == 84 && nd == 3 ? 2 : 1; }
+  // of them, those that pass through LDS at a time (Np = 84: all would be 166 KiB; 120: 90 KiB
+  // let one wave a SIMD in, and the compiler then used both register files, see above)
+  static constexpr int passes(int nd) { return NP >= 84 && nd == 3 ? 2 : 1; }
   static constexpr int acc_pass(bool last, int nd) { return (acc(last, nd) + passes(nd) - 1) / passes(nd); }
   static constexpr int lds_group(int nd) {
     return (acc_pass(true, nd) > acc_pass(false, nd) ? acc_pass(true, nd) : acc_pass(false, nd)) * WAVE;
   }
-  // (each row group of a workgroup has its own; rs workgroups share the groups)
-  static constexpr int lds_doubles(int nd, int rs) { return SLICES > 1 ? NRG / rs * lds_group(nd) : 1; }
+  // Column slices where rs workgroups share the row groups: at Np = 120 four workgroups
+  // of two groups have a second slice each, so that their four waves have half the columns.
+  static constexpr int slices(int rs) { return NP == 120 && rs == 4 ? 2 : SLICES; }
+  // (each row group of a workgroup has its own)
+  static constexpr int lds_doubles(int nd, int rs) { return slices(rs) > 1 ? NRG / rs * lds_group(nd) : 1; }
   // waves per SIMD the registers allow; partial sums: as many as run at once on
   // 256 CUs (a constant, not read from the device)
   static constexpr int WPS = NP <= 20 ? 4 : 2;
@@ -143,7 +147,8 @@ __device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t
 
   // this wave's columns, from c_lo: its slice of the part's range, which comes
   // in units of a whole number of DEPTH k-steps per slice
-  constexpr uint32_t UNIT = S::SLICES * DEPTH * CPS;
+  constexpr uint32_t SLICES = S::slices(RS);
+  constexpr uint32_t UNIT = SLICES * DEPTH * CPS;
   static_assert(GD_UNIT % UNIT == 0, "every part has a unit");
   const uint32_t nunits = (p.ncols + UNIT - 1) / UNIT;
   const uint32_t u_lo = (uint32_t)((uint64_t)part * nunits / p.npart);
@@ -418,7 +423,7 @@ __device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t
   auto store = [&](double v, uint32_t off, uint32_t common) __attribute__((always_inline)) {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rw, (int)off, (int)common, 0);
   };
-  if constexpr (S::SLICES == 1) {
+  if constexpr (SLICES == 1) {
     each([&](double v, int, uint32_t off, uint32_t common) __attribute__((always_inline)) { store(v, off, common); });
   } else {
     constexpr int PL = S::acc_pass(LAST, ND);
@@ -427,13 +432,13 @@ __device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t
     for (int pass = 0; pass < S::passes(ND); ++pass) {
       const int x0 = pass * PL;
 #pragma unroll 1
-      for (uint32_t v = 0; v < S::SLICES; ++v) {
+      for (uint32_t v = 0; v < SLICES; ++v) {
         if (slice == v) {
           if (v == 0)
             each([&](double a, int x, uint32_t, uint32_t) __attribute__((always_inline)) {
               if (x / PL == pass) mine[(x - x0) * WAVE] = a;
             });
-          else if (v + 1 < S::SLICES)
+          else if (v + 1 < SLICES)
             each([&](double a, int x, uint32_t, uint32_t) __attribute__((always_inline)) {
               if (x / PL == pass) mine[(x - x0) * WAVE] += a;
             });
@@ -451,9 +456,10 @@ __device__ __forceinline__ void gd_role(const GdArgs& p, uint32_t part, uint32_t
 // Forms: a workgroup per part (ND = 3, RS = 1); with few parts, RS = 2
 // workgroups of half the row groups each (grid.z), or those for each direction
 // (ND = 1, grid.y), so that the chain of products of a part is half or a sixth
-// as long (a sum of 2 parts, orders 5 / 6 / 7: 17 / 24 / 27 -> 8 / 12 / 11 us).
+// as long (a sum of 2 parts, orders 5 / 6 / 7: 17 / 24 / 27 -> 8 / 12 / 11 us); at
+// Np = 120 also RS = 4 with two column slices, a quarter.
 template <int NP, int ND, int RS>
-constexpr int gd_threads() { return GdShape<NP>::NTH / RS; }
+constexpr int gd_threads() { return WAVE * GdShape<NP>::NRG / RS * GdShape<NP>::slices(RS); }
 
 template <int NP, int ND, int RS>
 __global__ __launch_bounds__((gd_threads<NP, ND, RS>())) __attribute__((amdgpu_waves_per_eu(ND == 1 ? 3 : GdShape<NP>::WPS, 8)))
@@ -465,7 +471,7 @@ void gd_partial_kernel(GdArgs p) {
   if constexpr (S::NRG == 1) {
     slice = w0;
     rg = 0;
-  } else if constexpr (RS > 1) {  // half z has row groups z NRG / 2 on
+  } else if constexpr (RS > 1) {  // workgroup z has row groups z NRG / RS on
     constexpr uint32_t H = S::NRG / RS;
     slice = w0 / H;
     rg = w0 % H + blockIdx.z * H;
@@ -473,7 +479,7 @@ void gd_partial_kernel(GdArgs p) {
     slice = S::NRG == 2 ? w0 & 3u : S::NRG == 4 ? w0 >> 2 : 0u;
     rg = S::NRG == 2 ? w0 >> 2 : S::NRG == 4 ? (w0 + slice) & 3u : w0;
   }
-  double* mine = lds + (S::SLICES > 1 ? rg % (S::NRG / RS) * S::lds_group(ND) : 0);
+  double* mine = lds + (S::slices(RS) > 1 ? rg % (S::NRG / RS) * S::lds_group(ND) : 0);
   // (both kinds run the same number of workgroup barriers)
   if (S::NRG > 1 && rg + 1 < S::NRG)
     gd_role<NP, S::NRG == 1, ND, RS>(p, blockIdx.x, slice, (int)rg, (int)blockIdx.y, mine);

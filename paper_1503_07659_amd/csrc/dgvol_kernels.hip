@@ -471,8 +471,14 @@ static dg_status launch_gd_f64(const double* G, const double* u, const double* g
     // the finest form whose workgroups all have a CU of their own (of 256; at
     // Np = 35, of half a CU)
     if constexpr (NP >= 56) {
+      // At Np = 120 up to 64 parts: four workgroups a part, half the columns a wave
+      // (F = 3, 7.7e5 nodal values 40.6 -> 29.2 us, 9.8e5 41.4 -> 30.3; the kernel before
+      // this one: 35.7 and 36.0).
+      using I4 = std::integral_constant<int, NP == 120 ? 4 : 2>;
       if (npart <= 42)
         launch(I1{}, I2{});
+      else if (NP == 120 && npart <= 64)
+        launch(I3{}, I4{});
       else if (split_rows)
         launch(I3{}, I2{});
       else
