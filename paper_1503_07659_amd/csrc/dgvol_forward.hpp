@@ -409,8 +409,11 @@ __device__ __forceinline__ void fwd_f64_staged_multi(const FwdArgs<double>& p, u
   // The first run is requested before the operand table is built where the waves
   // take several, after it where most take one: there the table's own reads then
   // wait for it (order 2, F = 1, 1e5 nodal values 4.7 us, 5.5 with the request
-  // first; order 3, 1.35e6 14.1 against 14.5, 2e6 15.7 against 15.0).
-  const bool several = (uint64_t)nrun * 4 > (uint64_t)stride * 5;
+  // first).  Between, by what was measured (request first / last): F = 1, order 1, 1.9
+  // runs a wave 16.2 / 16.7 us, order 2, 1.5 13.7 / 14.3, order 3, 1.02 14.5 / 14.1; F >= 3,
+  // order 1, 1.6 11.7 / 11.3, order 2, 1.5 13.9 / 13.7, order 3, 1.3 15.2 / 14.7, 1.6 15.2 / 15.5.
+  const uint32_t quarters = p.F <= 2 ? 5 : NP == 20 ? 6 : 8;
+  const bool several = (uint64_t)nrun * 4 > (uint64_t)stride * quarters;
   if (several) load_run(t);
   build_fwd_table<NP, WPB>(p.D, afr);
   if (!several) load_run(t);
