@@ -147,7 +147,7 @@ dg_status dg_volume_adjoint_u(const double *D, const double *G, const double *go
  *   bytes, owned by the caller, 8-byte aligned; its contents on entry are
  *   ignored and on return are unspecified.  Calls that share one work buffer
  *   must be ordered on one stream.
- * The columns are split into a number of partial sums fixed by (K, F) alone
+ * The columns are split into a number of partial sums fixed by (K, F, Np) alone
  * and added in a fixed order, so the result is the same bit for bit on every
  * run and every device.  No D argument: gD does not depend on D.
  * Source: defined by this library, not by the paper (reverse mode of the
@@ -319,7 +319,7 @@ typedef struct dg_launch_shape {
   uint32_t resident;        /* workgroups the device holds at once (the persistent grid cap) */
   uint32_t units;           /* work units of the problem */
   uint32_t units_per_step;  /* units one workgroup takes per loop iteration */
-  uint32_t min_iters;       /* loop iterations of the least-loaded wave, over the operation's kernels */
+  uint32_t min_iters;       /* loop iterations of the least-loaded wave (0: a wave without tiles), over the operation's kernels */
   uint32_t max_iters;       /* loop iterations of the most-loaded wave, over the operation's kernels */
 } dg_launch_shape;
 

@@ -29,7 +29,8 @@
 //
 // Measured against the chunk-register body it replaced (u staged, outputs
 // assembled in LDS, two barriers per iteration), F = 3: order 6, K = 2^17
-// 387 -> 326 us (67 % of the FP64 matrix peak), 3e6 nodal values 49.3 -> 35.6
+// 387 -> 326 us (67 % of the FP64 matrix peak; on another card, warmer, 389 ->
+// 347), 3e6 nodal values 49.3 -> 35.6
 // us, K = 157, F = 17 17.3 -> 10.5 us; order 7, K = 2^16 322 -> 294 us (75 %),
 // 3e6 57.8 -> 51.2 us, K = 157, F = 1 18.0 -> 13.1 us.
 #pragma once

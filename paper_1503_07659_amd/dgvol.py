@@ -1,8 +1,8 @@
 """Python binding of libdgvol.so (argument marshalling only).
 
 The functions named like the C entry points (``dg_volume``,
-``dg_volume_adjoint``, ``dg_volume_grad_d``, ``dg_volume_grad_d_noalloc``, ``dg_volume_f32s``,
-``dg_volume_variant``, ``dg_volume_batched`` and the two calibration calls) take torch tensors on the
+``dg_volume_adjoint``, ``dg_volume_adjoint_u``, ``dg_volume_grad_d``, ``dg_volume_grad_d_noalloc``,
+``dg_volume_f32s``, ``dg_volume_variant``, ``dg_volume_batched`` and the calibration calls) take torch tensors on the
 GPU, check dtype/device/shape/contiguity, and pass raw device pointers plus
 torch's current HIP stream to the library.  Every arithmetic step runs in the
 HIP kernels; there is no CPU or PyTorch fallback: if the library is missing or
