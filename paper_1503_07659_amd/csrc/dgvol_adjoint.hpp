@@ -29,11 +29,12 @@ namespace dgvol {
 // = 56 with GG (266 of 64 and 112 of 16 cycles per tile, 80 % of the cycles
 // busy; the 250 FP64 multiply-adds of W and gG do not overlap them).  Measured
 // against the kernel it replaced (u, gout and gu exchanged through LDS, one
-// 8-wave workgroup per 8 tiles), F = 3, 2e7 nodal values: order 1 315 -> 231
-// us, order 2 215 -> 194, order 3 203 -> 189, order 4 221 -> 206; order 5,
-// K = 2^19 1105 -> 1083 us; order 3, K = 13601, F = 17 60 -> 48 us; 3e5
-// values: order 4 25 -> 13.5 us, order 5 40 -> 26 us.  gu alone, 2e7 values:
-// 135-165 us at orders 1-5.
+// 8-wave workgroup per 8 tiles), F = 3, 2e7 nodal values: order 1 315 -> 229
+// us, order 2 214 -> 192, order 3 203 -> 187, order 4 242 -> 208; order 5,
+// K = 2^19 1098 -> 1064 us; order 3, K = 13601, F = 17 61 -> 50 us; 1e6
+// values: order 2 15.6 -> 11.5 us, order 3 14.7 -> 14.0, order 4 27.5 -> 15.6,
+// order 5 49 -> 28; 3e5: order 4 24.5 -> 13.2, order 5 37.5 -> 25.9.  gu
+// alone, 2e7 values: 135-160 us at orders 1-5.
 //
 // GG = false: gu alone (no u, no recomputed D u, no gG), tiles dealt to the
 // waves in turn.  GG = true: each wave owns a contiguous run of whole elements

@@ -1,7 +1,7 @@
 // Adjoint at the high orders (Np = 84, 120) in two chunk-register passes.
 //
 // At these orders D (170-345 KB in FP64) does not fit in LDS, so the single
-// staged adjoint cannot hold its operand table.  As in the forward
+// adjoint of the lower orders cannot hold its operand table.  As in the forward
 // chunk-register body, the 8 waves of a workgroup each keep a share of D in
 // registers for the whole launch, and the workgroup stages the columns it
 // works on in LDS:
